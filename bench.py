@@ -37,7 +37,9 @@ def log(*a):
 
 # Sources of the step's kernels and of the slot structure they read (the
 # setup): the recorded traffic of a kernel is valid while these are unchanged.
-STEP_SOURCES = ("internal.h", "vec.h", "kernels.h", "compute.hip", "pack.hip", "plan.hip",
+STEP_SOURCES = ("internal.h", "vec.h", "kernels.h", "run.h", "compute.hip", "pack.hip",
+                "plan.hip", "inst_run_fused_f32.hip", "inst_run_fused_bf16.hip",
+                "inst_run_spmm_f32.hip", "inst_run_spmm_bf16.hip",
                 "inst_fused_f32.hip", "inst_fused_bf16.hip", "inst_sddmm_f32.hip",
                 "inst_sddmm_bf16.hip", "inst_spmm_f32.hip", "inst_spmm_bf16.hip")
 

@@ -293,7 +293,9 @@ spc3d_status spc3d_sddmm_spmm_scatter(spc3d_plan plan, const float* d_vals, cons
 
 /* spc3d_sddmm_spmm for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
- * the same computation and results, with the SpMM carries kept in a device
+ * the same computation and results (a default-variant call whose usual shape
+ * needs more carries than fit takes a shape with longer work items instead),
+ * with the SpMM carries kept in a device
  * array of SPC3D_STATIC_SCRATCH_BYTES that the library holds on each GPU it
  * runs on until the process ends, so no scratch argument is taken and nothing
  * is allocated or freed.  The caller still owns the inputs and outputs.

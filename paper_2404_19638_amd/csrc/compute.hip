@@ -1,9 +1,10 @@
 // SDDMM / SpMM entry points: argument checks, variant choice and launch.
 // The kernels and their design notes are in kernels.h; their instantiations
 // are spread over inst_*.hip so they compile in parallel.
+#include <cmath>
 #include <mutex>
 
-#include "kernels.h"
+#include "run.h"
 
 namespace spc3d {
 
@@ -16,8 +17,126 @@ SPC3D_EXTERN_LAUNCHERS(float, 1)
 SPC3D_EXTERN_LAUNCHERS(bf16_t, 8)
 SPC3D_EXTERN_LAUNCHERS(bf16_t, 1)
 #undef SPC3D_EXTERN_LAUNCHERS
+extern template void launch_run<float, 4, true>(SPC3D_RUN_LAUNCH_ARGS);
+extern template void launch_run<float, 4, false>(SPC3D_RUN_LAUNCH_ARGS);
+extern template void launch_run<bf16_t, 8, true>(SPC3D_RUN_LAUNCH_ARGS);
+extern template void launch_run<bf16_t, 8, false>(SPC3D_RUN_LAUNCH_ARGS);
 
 namespace {
+
+// Slices of a packed row that a pass takes one after another (1: the whole
+// row).  A pass over a large table is bound by the row lines that miss L2 (they
+// arrive at 6.5 to 7.5 TB/s from the Infinity Cache and HBM alike).  Where
+// columns are skewed, each XCD's 4 MB L2 holds the hot rows; of rows cut to a
+// 128- or 256-byte slice it holds two to four times as many, at the price of
+// reading the indices once per slice.  FP32 SpMM, R-MAT graphs of degree 32
+// (us, whole row / 256-byte / 128-byte slices): 2^20 vertices kz = 64 (157 MB
+// of rows) 775 / - / 643, kz = 128 1781 / 1473 / 1290; 2^19 kz = 128 743 / 631 /
+// 569; 2^18 kz = 128 (85 MB) 340 / 277 / 278, kz = 64 (42 MB) 141 / - / 145;
+// 2^17 kz = 128 (44 MB) 147 / 126 / 140, kz = 64 72 / - / 76.  Uniform
+// columns do not gain: 2^20 columns, 32 entries each, kz = 64 1248 / - / 1344.
+// So only blocks whose entries use fewer columns than uniform positions would
+// (0.8 of the expected number) are sliced.  The fused pass reads A and adds to
+// the dots once more per slice, so it slices only rows of 384 bytes or more of
+// tables beyond 128 MB: R-MAT 2^20 kz = 128 1867 / 1662 / 1712, 2^19 833 /
+// 767 / 874, 2^18 372 / 368 / 451, kz = 64 2^20 820 / - / 829.
+int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
+  const int64_t rows = transpose ? p->R : p->C;   // of the gathered table
+  const double ids = transpose ? (double)(p->row_hi - p->row_lo) : (double)(p->col_hi - p->col_lo);
+  if (row_bytes % 128 || rows >= 0.8 * ids * -expm1(-(double)p->nnz / ids)) return 1;
+  const int64_t lines = row_bytes / 128, table = rows * row_bytes;
+  constexpr int64_t MB = 1 << 20;
+  if (lines < (fused ? 3 : 2)) return 1;
+  if (table <= (fused ? 128 : lines == 2 ? 64 : 40) * MB) return 1;
+  if (lines % 2 == 0 && lines >= 4 && (fused || table / (lines / 2) <= 64 * MB))
+    return (int)(lines / 2);
+  return (int)lines;
+}
+
+// The run family's shape for a default-variant call, if it takes the call:
+// rows of 3 to 32 vectors (a lane of 8 then holds at most 4), byte offsets
+// into the packed operands of 32 bits and ids of 24 (one multiply-add per
+// gathered row).  Wider, narrower and larger operands keep the shapes of
+// pick_shape.
+//
+// Run length.  Longer runs mean fewer carries and scans, shorter ones more
+// wavefronts and less imbalance.  64 slots pay on rows of 16 entries and more
+// (fused pass, us at 32 / 64: R-MAT 2^18 kz = 64 171 / 166, 2^20 kz = 64 844 /
+// 815; at 9.5 entries a row kz = 32 80 / 86, at 3 (banded) kz = 128 357 / 381);
+// the SpMM alone, whose wavefronts are lighter, already gains at 8 (66.1 /
+// 63.8 at 9.5 entries, kz = 32), except at 4 vectors a lane (banded, 12
+// entries, kz = 128 524 / 574).  Below about 7000 wavefronts (7 per SIMD) the
+// shorter run is faster: R-MAT 2^16, kz = 32 at 16 / 32 / 64 slots 34.6 / 28.2 /
+// 33.6, 2^15 20.8 / 21.9 / 24.8.
+//
+// Rows of A.  With one vector a lane, loading the slot's row of A for every
+// slot (from L1 mostly) costs less than loading it under a mask where a row
+// starts, unless rows are long: 79.6 against 84.2 us on the 2^24-vertex share
+// (9.5 entries a row), 100.7 against 95.6 on R-MAT 2^18 (44), kz = 32.  With
+// more vectors a lane the L1 traffic decides: banded, 12 entries, kz = 128 892
+// against 682 us.
+bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, RunShape* sh) {
+  const int esz = t == SPC3D_F32 ? 4 : 2;
+  sh->vec = 16 / esz;
+  const int64_t most = p->R > p->C ? p->R : p->C;
+  if (kz < sh->vec || most >= (1 << 24) || most * kz * esz >= (int64_t(1) << 32)) return false;
+  sh->slices = slice_count(p, transpose, fused, (int64_t)kz * esz);
+  sh->kw = kz / sh->slices;
+  const int nvec = (sh->kw + sh->vec - 1) / sh->vec;
+  if (nvec < 3 || nvec > 32) return false;
+  sh->lanes = nvec <= 4 ? 4 : 8;
+  sh->nch = nvec <= 8 ? 1 : nvec <= 16 ? 2 : 4;
+  sh->full = sh->kw == sh->lanes * sh->nch * sh->vec;
+  const int64_t rows = transpose ? p->C : p->R;
+  const bool len16 = p->nnz >= 16 * rows;
+  sh->each_row = len16;
+  const int64_t G = 64 / sh->lanes;
+  const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);
+  sh->lg_s = long_runs && p->nnz >= 7000 * 64 * G ? 6 : p->nnz >= 7000 * 32 * G ? 5 : 4;
+  return true;
+}
+
+int64_t carry_bytes(int64_t nnz, int64_t item, int kz) {
+  const int64_t n = (nnz + item - 1) / item;
+  return (n > 0 ? n : 1) * 2 * kz * 4;
+}
+
+// Runs the pass through the run family.
+void run_family(const Plan* p, const RunShape& sh, int transpose, const float* d_vals,
+                const void* d_X, spc3d_dtype t, int kz, const YOut& Y, int acc, float* carry,
+                hipStream_t stream, const void* d_A, float* d_out) {
+  Orient o = transpose ? p->csc() : p->csr();
+  RunArgs a{};
+  a.nnz = p->nnz;
+  a.kz = kz;
+  a.idx = o.idx;
+  a.head = o.head;
+  a.tile_row = o.tile_row;
+  a.vals = d_vals;
+  a.vidx = transpose == 2 ? nullptr : o.vidx;
+  a.X = static_cast<const char*>(d_X);
+  a.A = static_cast<const char*>(d_A);
+  a.Y = Y;
+  a.carry = carry;
+  a.out = d_out;
+  a.acc_out = (acc & kAccOut) != 0;
+  const int outm = Y.map ? kAddSlab : (acc & kAccY) ? kAddPacked : kPut;
+  if (!d_A) {
+    if (t == SPC3D_F32)
+      launch_run<float, 4, false>(sh, a, outm, o.ptr, 0, sh.slices, stream);
+    else
+      launch_run<bf16_t, 8, false>(sh, a, outm, o.ptr, 0, sh.slices, stream);
+    return;
+  }
+  // each slice adds its part of the dots to the slices before it
+  for (int s = 0; s < sh.slices; ++s) {
+    if (s) a.acc_out = 1;
+    if (t == SPC3D_F32)
+      launch_run<float, 4, true>(sh, a, outm, o.ptr, s, 1, stream);
+    else
+      launch_run<bf16_t, 8, true>(sh, a, outm, o.ptr, s, 1, stream);
+  }
+}
 
 // Shared body of spc3d_spmm, spc3d_sddmm_spmm, spc3d_sddmm_spmm_static and
 // spc3d_sddmm_spmm_scatter.  Y: where finished rows go; acc: kAccY / kAccOut
@@ -32,9 +151,12 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
                   (!fused || aligned16(d_A));
   spc3d_status st = pick_shape(kz, x_t, al, variant, fused ? 2 : 1, p->nnz, &sh);
   if (st != SPC3D_OK) return st;
+  RunShape rs;
+  const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, &rs) &&
+                   buf_bytes >= (size_t)carry_bytes(p->nnz, rs.item(), kz);
   const int64_t nitems = (p->nnz + sh.items - 1) / sh.items;
   const size_t need = (size_t)nitems * 2 * (size_t)kz * 4;
-  if (buf_bytes < need) {
+  if (!run && buf_bytes < need) {
     if (static_buf)
       return fail(SPC3D_ERR_WORKSPACE,
                   "this call needs %zu bytes of scratch; the library's static scratch holds %zu "
@@ -47,6 +169,12 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
   st = dg.enter(p);
   if (st != SPC3D_OK) return st;
   SPC3D_DEBUG_CHECK(p, stream);
+  if (run) {
+    run_family(p, rs, transpose, d_vals, d_X, x_t, kz, Y, acc, static_cast<float*>(d_buf), stream,
+               d_A, d_out);
+    SPC3D_LAUNCHED(fused ? "sddmm_spmm" : "spmm");
+    return SPC3D_OK;
+  }
   const int64_t nblocks = (nitems + 3) / 4;
   Orient o = transpose ? p->csc() : p->csr();
   if (transpose == 2) o.vidx = nullptr;   // values already in column-major slot order
@@ -191,6 +319,14 @@ spc3d_status spc3d_spmm_buffer_size(spc3d_plan h, int transpose, int32_t kz, int
       }
   if (!any) return first;
   *bytes = (size_t)(items > 0 ? items : 1) * 2 * (size_t)kz * 4;
+  if (variant < 0)
+    for (int f = 0; f < 2; ++f)
+      for (int t = 0; t < 2; ++t) {
+        RunShape rs;
+        if (!pick_run(p, transpose, f != 0, kz, t ? SPC3D_BF16 : SPC3D_F32, &rs)) continue;
+        const size_t n = (size_t)carry_bytes(p->nnz, rs.item(), kz);
+        if (n > *bytes) *bytes = n;
+      }
   return SPC3D_OK;
 }
 

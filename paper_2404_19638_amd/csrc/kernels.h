@@ -864,6 +864,9 @@ inline int pow2ceil(int n) {
   return p;
 }
 
+// Default-variant SpMM and fused calls take the run family (run.h) where it
+// covers them; the SpMM and fused defaults below serve the others.
+//
 // op: 0 SDDMM, 1 SpMM, 2 fused SDDMM+SpMM.  Defaults (variant -1), from
 // measurements on MI355X: SDDMM on 64-slot work items with lanes covering kz
 // (8 lanes for 16-byte FP32 rows of 16 or more vectors below 2^20 entries); SpMM and

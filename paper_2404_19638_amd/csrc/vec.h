@@ -84,4 +84,10 @@ struct Unpack<bf16_t, 8> {
   }
 };
 
+template <typename T, int VEC, int NCH>
+__device__ inline void unpack_raw(const uint4 (&r)[NCH], float (&o)[NCH][VEC]) {
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) Unpack<T, VEC>::run(r[ch], o[ch]);
+}
+
 }  // namespace spc3d
