@@ -6,8 +6,16 @@
 // rows (or columns) in local-id order, and unpacking reduces (+=) into the
 // owner's rows as the SpMM PostComm does ("Building SpMM with SpComm3D").
 //
-// Both kernels stream in 16-byte chunks (4 FP32 or 8 bfloat16 values), so a
-// packed FP32 row with kz = 32 is one 128-byte line.
+// Both kernels move a row in chunks of 16 bytes of packed data (4 FP32 or 8
+// bfloat16 values; 32 bytes of an FP32 source converted to bfloat16).  A
+// wavefront takes `rpw` consecutive rows: it loads their global ids in one
+// access, then walks the rows' chunks as one sequence (chunk j of the group is
+// chunk j % c of row j / c), all lanes busy whatever the width, kBatch chunks
+// a lane loaded before the first is stored.  The last chunk of a row whose
+// width is not a multiple of a chunk is moved back to end with the row; a
+// gather then writes the shared elements twice with the same value, a scatter
+// leaves them to the chunk before.  Rows and buffers need the element's
+// alignment only.
 #include <type_traits>
 
 #include "internal.h"
@@ -15,147 +23,220 @@
 
 namespace spc3d {
 
-// Each thread moves kUnroll chunks of VO output elements, all loads of a
-// thread issued before its stores (1 measured best: more threads in flight).
-constexpr int kUnroll = 1;
+constexpr int kBatch = 2;
 
-template <typename Tin, typename Tout, int VO>
-struct Chunk;
+// What bounds both: the slab rows, which are read once from HBM, through an
+// Infinity Cache full of the step's other data.  Reading them nontemporal
+// keeps them from evicting it: an R-MAT share's gather (115 MB) takes 25.8 us
+// against 36.5 after 400 MB of other writes.  Nontemporal stores of what the
+// next kernels read again pay only once it outgrows the caches: packed rows
+// beyond 128 MB (uniform share, 229 MB an operand, whole step 418 to 409 us;
+// R-MAT share, 55 MB, 167 to 169), slab rows beyond 32 MB (R-MAT share 52 MB
+// 177 to 167; 2^18 rows kz = 30, 18 MB, 166.5 to 169).  Before, one 16-byte
+// chunk a thread at cached accesses, or one element a thread where the width or
+// an address was not a multiple of 16 bytes (whole step, before and after: R-MAT
+// share 173 to 167, uniform 416 to 409, banded bfloat16 820 to 781, kz = 30 182
+// to 167).
+constexpr int64_t kStreamPacked = 128 << 20;
+constexpr int64_t kStreamSlab = 32 << 20;
 
-template <>
-struct Chunk<float, float, 4> {
-  float4 v;
-  __device__ void load(const float* s) { v = *reinterpret_cast<const float4*>(s); }
-  __device__ void store(float* d) const { *reinterpret_cast<float4*>(d) = v; }
-};
+typedef uint32_t vec4u_e4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t vec4u_e2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef float vec4f_e4 __attribute__((ext_vector_type(4), aligned(4)));
 
-template <>
-struct Chunk<float, bf16_t, 8> {
-  float4 a, b;
-  __device__ void load(const float* s) {
-    a = reinterpret_cast<const float4*>(s)[0];
-    b = reinterpret_cast<const float4*>(s)[1];
+// The rows a wavefront moves.
+struct RowGroup {
+  int64_t r0;      // first local row
+  int64_t off;     // of row r0 + lane: first element in the slab
+  int total;       // chunks
+  __device__ inline RowGroup(int64_t n, int rpw, int c, const int64_t* __restrict__ gmap,
+                             int64_t lo, int64_t ld, int k0) {
+    const int lane = threadIdx.x & 63;
+    r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * rpw;
+    const int rows = n - r0 < rpw ? (n > r0 ? (int)(n - r0) : 0) : rpw;
+    off = lane < rows ? (gmap[r0 + lane] - lo) * ld + k0 : 0;
+    total = rows * c;
   }
-  __device__ void store(bf16_t* d) const {
-    uint4 o;
-    o.x = (uint32_t)f32_to_bf16(a.x) | ((uint32_t)f32_to_bf16(a.y) << 16);
-    o.y = (uint32_t)f32_to_bf16(a.z) | ((uint32_t)f32_to_bf16(a.w) << 16);
-    o.z = (uint32_t)f32_to_bf16(b.x) | ((uint32_t)f32_to_bf16(b.y) << 16);
-    o.w = (uint32_t)f32_to_bf16(b.z) | ((uint32_t)f32_to_bf16(b.w) << 16);
-    *reinterpret_cast<uint4*>(d) = o;
+};
+
+// Row and first element of chunk j.  magic = ceil(2^32 / c): exact for the
+// j < 64 * 256 of a group.
+struct ChunkAt {
+  int l, e;
+  __device__ inline ChunkAt(int j, int c, uint32_t magic, int vo, int kz) {
+    l = c == 1 ? j : (int)__umulhi((uint32_t)j, magic);
+    const int w = (j - l * c) * vo;
+    e = w < kz - vo ? w : kz - vo;
   }
 };
 
-template <>
-struct Chunk<bf16_t, bf16_t, 8> {
-  uint4 v;
-  __device__ void load(const bf16_t* s) { v = *reinterpret_cast<const uint4*>(s); }
-  __device__ void store(bf16_t* d) const { *reinterpret_cast<uint4*>(d) = v; }
-};
-
-template <>
-struct Chunk<float, float, 1> {
-  float v;
-  __device__ void load(const float* s) { v = *s; }
-  __device__ void store(float* d) const { *d = v; }
-};
-
-template <>
-struct Chunk<float, bf16_t, 1> {
-  float v;
-  __device__ void load(const float* s) { v = *s; }
-  __device__ void store(bf16_t* d) const { *d = f32_to_bf16(v); }
-};
-
-template <>
-struct Chunk<bf16_t, bf16_t, 1> {
-  bf16_t v;
-  __device__ void load(const bf16_t* s) { v = *s; }
-  __device__ void store(bf16_t* d) const { *d = v; }
-};
-
-// packed[l*kz + k] = conv(src[(gmap[l]-lo)*ld + k0 + k]), VO elements per chunk.
-template <typename Tin, typename Tout, int VO>
-__global__ __launch_bounds__(256) void k_gather(int64_t n, const int64_t* __restrict__ gmap,
-                                                int64_t lo, const Tin* __restrict__ src,
-                                                int64_t ld, int k0, int kz,
-                                                Tout* __restrict__ dst) {
-  const int chunks = kz / VO;
-  const int64_t total = n * chunks;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * kUnroll;
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x * kUnroll + threadIdx.x; base < total;
-       base += stride) {
-    Chunk<Tin, Tout, VO> c[kUnroll];
-    int64_t at[kUnroll];
+// packed[l*kz + k] = conv(src[(gmap[l]-lo)*ld + k0 + k]).
+template <typename Tin, typename Tout, bool NT>
+__global__ __launch_bounds__(256) void k_gather(int64_t n, int rpw, int c, uint32_t magic,
+                                                const int64_t* __restrict__ gmap, int64_t lo,
+                                                const Tin* __restrict__ src, int64_t ld, int k0,
+                                                int kz, Tout* __restrict__ dst) {
+  constexpr int VO = 16 / sizeof(Tout);
+  constexpr int NL = VO * sizeof(Tin) / 16;   // 16-byte loads of a chunk
+  using VI = typename std::conditional<sizeof(Tin) == 4, vec4u_e4, vec4u_e2>::type;
+  using VOUT = typename std::conditional<sizeof(Tout) == 4, vec4u_e4, vec4u_e2>::type;
+  const RowGroup rg(n, rpw, c, gmap, lo, ld, k0);
+  const int lane = threadIdx.x & 63;
+  Tout* out = dst + rg.r0 * kz;
+  for (int base = 0; base < rg.total; base += 64 * kBatch) {
+    VI v[kBatch][NL];
+    int at[kBatch];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int64_t i = base + (int64_t)u * blockDim.x;
-      at[u] = i;
-      if (i < total) {
-        const int64_t l = i / chunks;
-        const int ci = (int)(i - l * chunks);
-        c[u].load(src + (gmap[l] - lo) * ld + k0 + (int64_t)ci * VO);
-      }
+    for (int i = 0; i < kBatch; ++i) {
+      const int j0 = base + i * 64 + lane;
+      const int j = j0 < rg.total ? j0 : rg.total - 1;   // spare lanes repeat the last chunk
+      const ChunkAt ch(j, c, magic, VO, kz);
+      const VI* s = reinterpret_cast<const VI*>(src + __shfl(rg.off, ch.l) + ch.e);
+#pragma unroll
+      for (int h = 0; h < NL; ++h) v[i][h] = __builtin_nontemporal_load(s + h);
+      at[i] = ch.l * kz + ch.e;
     }
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      if (at[u] < total) {
-        const int64_t l = at[u] / chunks;
-        const int ci = (int)(at[u] - l * chunks);
-        c[u].store(dst + l * kz + (int64_t)ci * VO);
-      }
-    }
-  }
-}
-
-// dst[(gmap[l]-lo)*ld + k0 + k] += packed[l*kz + k]; VO elements per chunk.
-template <int VO>
-__global__ __launch_bounds__(256) void k_scatter_add(int64_t n, const int64_t* __restrict__ gmap,
-                                                     int64_t lo, const float* __restrict__ packed,
-                                                     int kz, float* __restrict__ dst, int64_t ld,
-                                                     int k0) {
-  using V = typename std::conditional<VO == 4, float4, float>::type;
-  const int chunks = kz / VO;
-  const int64_t total = n * chunks;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x * kUnroll;
-  for (int64_t base = (int64_t)blockIdx.x * blockDim.x * kUnroll + threadIdx.x; base < total;
-       base += stride) {
-    V a[kUnroll], b[kUnroll];
-    float* d[kUnroll];
+    for (int i = 0; i < kBatch; ++i) {
+      VOUT o;
+      if constexpr (sizeof(Tin) == sizeof(Tout)) {
+        o = v[i][0];
+      } else {
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const int64_t i = base + (int64_t)u * blockDim.x;
-      d[u] = nullptr;
-      if (i < total) {
-        const int64_t l = i / chunks;
-        const int ci = (int)(i - l * chunks);
-        d[u] = dst + (gmap[l] - lo) * ld + k0 + (int64_t)ci * VO;
-        a[u] = *reinterpret_cast<const V*>(d[u]);
-        b[u] = *reinterpret_cast<const V*>(packed + l * kz + (int64_t)ci * VO);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      if (d[u]) {
-        V r = a[u];
-        if constexpr (VO == 4) {
-          r.x = a[u].x + b[u].x; r.y = a[u].y + b[u].y; r.z = a[u].z + b[u].z; r.w = a[u].w + b[u].w;
-        } else {
-          r = a[u] + b[u];
+        for (int t = 0; t < 4; ++t) {
+          const VI w = v[i][t >> 1];
+          o[t] = (uint32_t)f32_to_bf16(__uint_as_float(w[(t & 1) * 2])) |
+                 ((uint32_t)f32_to_bf16(__uint_as_float(w[(t & 1) * 2 + 1])) << 16);
         }
-        *reinterpret_cast<V*>(d[u]) = r;
+      }
+      VOUT* d = reinterpret_cast<VOUT*>(out + at[i]);
+      if constexpr (NT)
+        __builtin_nontemporal_store(o, d);
+      else
+        *d = o;
+    }
+  }
+}
+
+// dst[(gmap[l]-lo)*ld + k0 + k] += packed[l*kz + k].
+template <bool NT>
+__global__ __launch_bounds__(256) void k_scatter_add(int64_t n, int rpw, int c, uint32_t magic,
+                                                     const int64_t* __restrict__ gmap, int64_t lo,
+                                                     const float* __restrict__ packed, int kz,
+                                                     float* __restrict__ dst, int64_t ld, int k0) {
+  const RowGroup rg(n, rpw, c, gmap, lo, ld, k0);
+  const int lane = threadIdx.x & 63;
+  const float* in = packed + rg.r0 * kz;
+  for (int base = 0; base < rg.total; base += 64 * kBatch) {
+    vec4f_e4 v[kBatch], w[kBatch];
+    float* at[kBatch];
+    int skip[kBatch];   // leading elements that are another lane's
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const int j0 = base + i * 64 + lane;
+      const int j = j0 < rg.total ? j0 : rg.total - 1;
+      const ChunkAt ch(j, c, magic, 4, kz);
+      skip[i] = j0 < rg.total ? (j - ch.l * c) * 4 - ch.e : 4;
+      at[i] = dst + __shfl(rg.off, ch.l) + ch.e;
+      const vec4f_e4* p = reinterpret_cast<const vec4f_e4*>(in + ch.l * kz + ch.e);
+      const vec4f_e4* d = reinterpret_cast<const vec4f_e4*>(at[i]);
+      v[i] = __builtin_nontemporal_load(p);   // read for the last time
+      w[i] = NT ? __builtin_nontemporal_load(d) : *d;
+    }
+#pragma unroll
+    for (int i = 0; i < kBatch; ++i) {
+      const vec4f_e4 s = w[i] + v[i];
+      vec4f_e4* d = reinterpret_cast<vec4f_e4*>(at[i]);
+      if (skip[i] == 0) {
+        if constexpr (NT)
+          __builtin_nontemporal_store(s, d);
+        else
+          *d = s;
+      } else {
+#pragma unroll
+        for (int t = 1; t < 4; ++t)
+          if (t >= skip[i]) at[i][t] = s[t];
       }
     }
   }
 }
 
-static unsigned grid_chunks(int64_t total) {
-  int64_t b = (total + 256 * kUnroll - 1) / (256 * kUnroll);
-  if (b < 1) b = 1;
-  if (b > (1 << 20)) b = 1 << 20;
-  return (unsigned)b;
+// Rows narrower than a chunk: one element a thread.
+template <typename Tin, typename Tout>
+__global__ __launch_bounds__(256) void k_gather_narrow(int64_t n, const int64_t* __restrict__ gmap,
+                                                       int64_t lo, const Tin* __restrict__ src,
+                                                       int64_t ld, int k0, int kz,
+                                                       Tout* __restrict__ dst) {
+  const int64_t total = n * kz;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t l = i / kz;
+    const Tin v = src[(gmap[l] - lo) * ld + k0 + (i - l * kz)];
+    if constexpr (sizeof(Tin) == sizeof(Tout))
+      dst[i] = v;
+    else
+      dst[i] = f32_to_bf16(v);
+  }
 }
 
+__global__ __launch_bounds__(256) void k_scatter_add_narrow(int64_t n,
+                                                            const int64_t* __restrict__ gmap,
+                                                            int64_t lo,
+                                                            const float* __restrict__ packed,
+                                                            int kz, float* __restrict__ dst,
+                                                            int64_t ld, int k0) {
+  const int64_t total = n * kz;
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t l = i / kz;
+    dst[(gmap[l] - lo) * ld + k0 + (i - l * kz)] += packed[i];
+  }
+}
+
+namespace {
+
+unsigned blocks_narrow(int64_t total) {
+  const int64_t b = (total + 255) / 256;
+  return (unsigned)(b < 1 ? 1 : b > (1 << 20) ? 1 << 20 : b);
+}
+
+// Rows per wavefront: as many as fill its kBatch chunks a lane.  More rows a
+// wavefront were slower (banded block, 2.1M rows of 64 bfloat16 values, whole
+// step: 811 us with 32 rows of 16 chunks each against 781).
+struct RowSplit {
+  int rpw, c;
+  uint32_t magic;
+  dim3 grid;
+  RowSplit(int64_t n, int kz, int vo) {
+    c = (kz + vo - 1) / vo;
+    magic = c == 1 ? 0u : (uint32_t)(((1ull << 32) + c - 1) / c);
+    rpw = 64 * kBatch / c;
+    rpw = rpw < 1 ? 1 : rpw > 64 ? 64 : rpw;
+    grid = dim3((unsigned)(((n + rpw - 1) / rpw + 3) / 4));
+  }
+};
+
+template <typename Tin, typename Tout>
+void launch_gather(int64_t n, const int64_t* gmap, int64_t lo, const void* src, int64_t ld, int k0,
+                   int kz, void* dst, hipStream_t stream) {
+  constexpr int VO = 16 / sizeof(Tout);
+  const Tin* s = static_cast<const Tin*>(src);
+  Tout* d = static_cast<Tout*>(dst);
+  if (kz < VO) {
+    hipLaunchKernelGGL((k_gather_narrow<Tin, Tout>), dim3(blocks_narrow(n * kz)), dim3(256), 0,
+                       stream, n, gmap, lo, s, ld, k0, kz, d);
+    return;
+  }
+  const RowSplit sp(n, kz, VO);
+  if (n * kz * (int64_t)sizeof(Tout) > kStreamPacked)
+    hipLaunchKernelGGL((k_gather<Tin, Tout, true>), sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
+                       sp.magic, gmap, lo, s, ld, k0, kz, d);
+  else
+    hipLaunchKernelGGL((k_gather<Tin, Tout, false>), sp.grid, dim3(256), 0, stream, n, sp.rpw,
+                       sp.c, sp.magic, gmap, lo, s, ld, k0, kz, d);
+}
+
+}  // namespace
 }  // namespace spc3d
 
 using namespace spc3d;
@@ -187,35 +268,12 @@ spc3d_status spc3d_gather(spc3d_plan h, spc3d_axis axis, const void* d_src, spc3
   SPC3D_DEBUG_CHECK(p, stream);
   const int64_t* gmap = axis == SPC3D_ROWS ? p->gmap_r : p->gmap_c;
   const int64_t lo = axis == SPC3D_ROWS ? p->row_lo : p->col_lo;
-  const bool src_al = aligned16(d_src) && aligned16(d_packed);
-  if (src_t == SPC3D_F32 && packed_t == SPC3D_F32) {
-    const float* s = static_cast<const float*>(d_src);
-    float* d = static_cast<float*>(d_packed);
-    if (src_al && kz % 4 == 0 && ld_src % 4 == 0 && k0 % 4 == 0)
-      hipLaunchKernelGGL((k_gather<float, float, 4>), dim3(grid_chunks(n * kz / 4)), dim3(256), 0,
-                         stream, n, gmap, lo, s, ld_src, k0, kz, d);
-    else
-      hipLaunchKernelGGL((k_gather<float, float, 1>), dim3(grid_chunks(n * kz)), dim3(256), 0,
-                         stream, n, gmap, lo, s, ld_src, k0, kz, d);
-  } else if (src_t == SPC3D_F32) {
-    const float* s = static_cast<const float*>(d_src);
-    bf16_t* d = static_cast<bf16_t*>(d_packed);
-    if (src_al && kz % 8 == 0 && ld_src % 4 == 0 && k0 % 4 == 0)
-      hipLaunchKernelGGL((k_gather<float, bf16_t, 8>), dim3(grid_chunks(n * kz / 8)), dim3(256),
-                         0, stream, n, gmap, lo, s, ld_src, k0, kz, d);
-    else
-      hipLaunchKernelGGL((k_gather<float, bf16_t, 1>), dim3(grid_chunks(n * kz)), dim3(256), 0,
-                         stream, n, gmap, lo, s, ld_src, k0, kz, d);
-  } else {
-    const bf16_t* s = static_cast<const bf16_t*>(d_src);
-    bf16_t* d = static_cast<bf16_t*>(d_packed);
-    if (src_al && kz % 8 == 0 && ld_src % 8 == 0 && k0 % 8 == 0)
-      hipLaunchKernelGGL((k_gather<bf16_t, bf16_t, 8>), dim3(grid_chunks(n * kz / 8)), dim3(256),
-                         0, stream, n, gmap, lo, s, ld_src, k0, kz, d);
-    else
-      hipLaunchKernelGGL((k_gather<bf16_t, bf16_t, 1>), dim3(grid_chunks(n * kz)), dim3(256), 0,
-                         stream, n, gmap, lo, s, ld_src, k0, kz, d);
-  }
+  if (src_t == SPC3D_BF16)
+    launch_gather<bf16_t, bf16_t>(n, gmap, lo, d_src, ld_src, k0, kz, d_packed, stream);
+  else if (packed_t == SPC3D_BF16)
+    launch_gather<float, bf16_t>(n, gmap, lo, d_src, ld_src, k0, kz, d_packed, stream);
+  else
+    launch_gather<float, float>(n, gmap, lo, d_src, ld_src, k0, kz, d_packed, stream);
   SPC3D_LAUNCHED("gather");
   return SPC3D_OK;
 }
@@ -240,12 +298,18 @@ spc3d_status spc3d_scatter_reduce(spc3d_plan h, spc3d_axis axis, const float* d_
   SPC3D_DEBUG_CHECK(p, stream);
   const int64_t* gmap = axis == SPC3D_ROWS ? p->gmap_r : p->gmap_c;
   const int64_t lo = axis == SPC3D_ROWS ? p->row_lo : p->col_lo;
-  if (aligned16(d_packed) && aligned16(d_dst) && kz % 4 == 0 && ld_dst % 4 == 0 && k0 % 4 == 0)
-    hipLaunchKernelGGL(k_scatter_add<4>, dim3(grid_chunks(n * kz / 4)), dim3(256), 0, stream, n,
+  if (kz < 4) {
+    hipLaunchKernelGGL(k_scatter_add_narrow, dim3(blocks_narrow(n * kz)), dim3(256), 0, stream, n,
                        gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
-  else
-    hipLaunchKernelGGL(k_scatter_add<1>, dim3(grid_chunks(n * kz)), dim3(256), 0, stream, n,
-                       gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
+  } else {
+    const RowSplit sp(n, kz, 4);
+    if (n * kz * 4 > kStreamSlab)
+      hipLaunchKernelGGL(k_scatter_add<true>, sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
+                         sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
+    else
+      hipLaunchKernelGGL(k_scatter_add<false>, sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
+                         sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
+  }
   SPC3D_LAUNCHED("scatter_reduce");
   return SPC3D_OK;
 }
