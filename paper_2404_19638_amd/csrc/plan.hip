@@ -4,13 +4,22 @@
 // blocks and the two maps) and Section "General structure" (a setup phase run
 // once per sparsity pattern, after which iterations only move data).
 //
-// Device pipeline, all HBM-streaming:
-//   mark ids      flag[g - lo] = 1 for every id (range violations raise a flag)
-//   scan flags    lmap[g - lo] = exclusive prefix or -1; gmap[rank] = g
-//   key/value     key = lr << bits(C) | lc, value = caller index
+// Device pipeline, both axes in each of the first five launches:
+//   mark ids      one byte flag per id of the range (range violations raise a
+//                 flag of their own)
+//   rank words    64 flags to a bitmap word with the number of ids before it
+//   compact       lmap[g - lo] = rank or -1; gmap[rank] = g
+//   key/value     key = lr << bits(C) | lc (ranks from the words, which fit L2
+//                 where localMap would not), value = caller index
 //   radix sort    LSD, 8-bit digits, stable (so equal keys keep caller order)
 //   build slots   colidx, perm, rowptr, per-64-slot head bitmaps and tile rows
-// and the same sort again on (lc, lr) for the column-major view.
+// For the column-major view the slots are sorted again by column alone: the
+// sort is stable and the slots ascend by row.
+// What bounds setup: the sort's passes, and 2 random accesses an entry in each
+// of marking and key construction (a 128-byte line each, from L2).  An R-MAT
+// share of 4.1M entries (ranges of 2^21) took 677 us before and takes 464 after the
+// byte flags, rank words and sort described below, with the value permutation
+// (59 us); a CSR graph of 1.8M entries with both views 526 and 323.
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -64,10 +73,6 @@ spc3d_status DeviceGuard::enter(const Plan* p) {
 
 // ------------------------------------------------------------- kernels
 
-constexpr int kScanThreads = 256;
-constexpr int kScanItems = 16;
-constexpr int kScanTile = kScanThreads * kScanItems;   // 4096
-
 __device__ inline int wave_inclusive_sum(int v) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
@@ -104,234 +109,403 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
     p[i] = v;
 }
 
-__global__ void k_mark(int64_t nnz, const int64_t* __restrict__ gid, int64_t lo, int64_t hi,
-                       int32_t* __restrict__ flag, int32_t* __restrict__ err) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < nnz;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t g = gid[p];
-    if (g < lo || g >= hi) {
+// One axis of a block during localization.
+struct Axis {
+  const int64_t* gid;    // nullptr: flags were set from a CSR row pointer
+  int64_t lo, range;
+  uint8_t* flag;         // one byte per id, in the localMap's memory
+  struct RankWord* word;
+  int32_t* partial;      // ids of each tile of kWordTile ids
+  int32_t* lmap;
+  int64_t* gmap;
+  int32_t* count;        // ids in use
+};
+
+// 64 ids: which are in use, and how many in use come before them.
+struct alignas(16) RankWord {
+  uint64_t bits;
+  int32_t before;
+  int32_t pad;
+};
+
+constexpr int kWordTile = 256 * 64;   // ids per block of k_rank_words
+
+__device__ inline int rank_of(const RankWord* __restrict__ word, int64_t id) {
+  const RankWord w = word[id >> 6];
+  return w.before + __popcll(w.bits & ((1ull << (id & 63)) - 1ull));
+}
+
+__global__ __launch_bounds__(256) void k_clear_flags(Axis r, Axis c) {
+  const Axis& ax = blockIdx.y ? c : r;
+  uint4* p = reinterpret_cast<uint4*>(ax.flag);
+  const int64_t n = (ax.range + 15) / 16;   // the memory holds 4 bytes per id
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    p[i] = make_uint4(0, 0, 0, 0);
+}
+
+// Flags every id.  Reading a flag first to store only where it is clear was
+// slower (89 against 58 us for 2 x 4.1M ids in ranges of 2^21): a random read
+// moves a 128-byte line into L1, a store one byte.
+__global__ __launch_bounds__(256) void k_mark(int64_t nnz, Axis r, Axis c,
+                                              int32_t* __restrict__ err) {
+  const Axis& ax = blockIdx.y ? c : r;
+  if (!ax.gid) return;
+  constexpr int U = 4;
+  const int64_t p0 = blockIdx.x * (int64_t)(256 * U) + threadIdx.x;
+  int64_t g[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t p = p0 + u * 256;
+    g[u] = p < nnz ? __builtin_nontemporal_load(ax.gid + p) - ax.lo : -1;
+    if (p < nnz && (g[u] < 0 || g[u] >= ax.range)) {
       err[0] = 1;
-    } else {
-      flag[g - lo] = 1;
+      g[u] = -1;
     }
   }
-}
-
-// Block sums of in[] over tiles of kScanTile.
-__global__ __launch_bounds__(kScanThreads) void k_scan_reduce(const int32_t* __restrict__ in,
-                                                              int64_t n,
-                                                              int32_t* __restrict__ partial) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int s = 0;
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    int64_t j = base + (int64_t)i * kScanThreads + threadIdx.x;
-    s += (j < n) ? in[j] : 0;
-  }
-  int tot;
-  block_exclusive_sum<kScanThreads>(s, &tot);
-  if (threadIdx.x == 0) partial[blockIdx.x] = tot;
+  for (int u = 0; u < U; ++u)
+    if (g[u] >= 0) ax.flag[g[u]] = 1;
 }
 
-// Exclusive scan of partial[0..m) in place by one block; total -> *total.
-__global__ __launch_bounds__(1024) void k_scan_partials(int32_t* partial, int64_t m,
-                                                        int32_t* total) {
+// Bitmap word and ids before it inside the tile; the tile's total to partial.
+__global__ __launch_bounds__(256) void k_rank_words(Axis r, Axis c) {
+  const Axis& ax = blockIdx.y ? c : r;
+  const int64_t w = blockIdx.x * (int64_t)256 + threadIdx.x;
+  if (blockIdx.x * (int64_t)kWordTile >= ax.range) return;   // uniform per block
+  uint64_t bits = 0;
+  if (w * 64 < ax.range) {
+    const uint4* p = reinterpret_cast<const uint4*>(ax.flag + w * 64);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (w * 64 + i * 16 >= ax.range) break;   // past the cleared flags
+      const uint4 v = p[i];
+      const uint64_t a = v.x | ((uint64_t)v.y << 32), b = v.z | ((uint64_t)v.w << 32);
+      // eight 0/1 bytes to eight bits
+      const uint64_t m = ((a * 0x0102040810204080ull) >> 56) |
+                         (((b * 0x0102040810204080ull) >> 56) << 8);
+      bits |= m << (i * 16);
+    }
+  }
+  int total;
+  const int before = block_exclusive_sum<256>(__popcll(bits), &total);
+  if (w * 64 < ax.range) {
+    RankWord o;
+    o.bits = bits;
+    o.before = before;
+    o.pad = 0;
+    ax.word[w] = o;
+  }
+  if (threadIdx.x == 0) ax.partial[blockIdx.x] = total;
+}
+
+// Exclusive scan of each axis' partials in place; the totals are the counts.
+__global__ __launch_bounds__(1024) void k_scan_partials(Axis r, Axis c) {
+  const Axis& ax = blockIdx.x ? c : r;
+  const int64_t m = (ax.range + kWordTile - 1) / kWordTile;
   int carry = 0;
   for (int64_t base = 0; base < m; base += 1024) {
-    int64_t j = base + threadIdx.x;
-    int v = (j < m) ? partial[j] : 0;
+    const int64_t j = base + threadIdx.x;
+    const int v = (j < m) ? ax.partial[j] : 0;
     int tot;
-    int ex = block_exclusive_sum<1024>(v, &tot);
-    if (j < m) partial[j] = carry + ex;
+    const int ex = block_exclusive_sum<1024>(v, &tot);
+    if (j < m) ax.partial[j] = carry + ex;
     carry += tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0 && total) *total = carry;
+  if (threadIdx.x == 0) *ax.count = carry;
 }
 
-// Blocked per-thread prefix within a tile: thread t owns items
-// [t*kScanItems, (t+1)*kScanItems) of the tile.
-struct TileScan {
-  int v[kScanItems];
-  int ex[kScanItems];
-};
-
-__device__ inline void tile_exclusive(const int32_t* __restrict__ in, int64_t n, int64_t base,
-                                      int offset, TileScan& ts) {
-  int s = 0;
+// Words -> localMap (rank or -1) and globalMap (rank -> global id); the words'
+// counts become global.  A wavefront takes kCompactWords words, lane i id i of
+// each.
+constexpr int kCompactWords = 16;
+__global__ __launch_bounds__(256) void k_compact(Axis r, Axis c) {
+  const Axis& ax = blockIdx.y ? c : r;
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (ax.range + 63) / 64;
+  const int64_t w0 = (blockIdx.x * (int64_t)4 + (threadIdx.x >> 6)) * kCompactWords;
+  if (w0 >= nw) return;
+  const int nwd = nw - w0 < kCompactWords ? (int)(nw - w0) : kCompactWords;
+  RankWord mine;
+  mine.bits = 0;
+  mine.before = 0;
+  mine.pad = 0;
+  if (lane < nwd) {
+    mine = ax.word[w0 + lane];
+    mine.before += ax.partial[(w0 + lane) / 256];
+    ax.word[w0 + lane] = mine;
+  }
 #pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    int64_t j = base + (int64_t)threadIdx.x * kScanItems + i;
-    ts.v[i] = (j < n) ? in[j] : 0;
-    s += ts.v[i];
-  }
-  int tot;
-  int ex = block_exclusive_sum<kScanThreads>(s, &tot) + offset;
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    ts.ex[i] = ex;
-    ex += ts.v[i];
-  }
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_scan_down(const int32_t* in, int64_t n,
-                                                            const int32_t* __restrict__ partial,
-                                                            int32_t* out) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  TileScan ts;
-  tile_exclusive(in, n, base, partial[blockIdx.x], ts);
-  __syncthreads();   // in and out may alias
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    int64_t j = base + (int64_t)threadIdx.x * kScanItems + i;
-    if (j < n) out[j] = ts.ex[i];
-  }
-}
-
-// Flags -> localMap (rank or -1) and globalMap (rank -> global id).
-__global__ __launch_bounds__(kScanThreads) void k_compact(int32_t* lmap, int64_t n, int64_t lo,
-                                                          const int32_t* __restrict__ partial,
-                                                          int64_t* __restrict__ gmap) {
-  const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  TileScan ts;
-  tile_exclusive(lmap, n, base, partial[blockIdx.x], ts);
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kScanItems; ++i) {
-    int64_t j = base + (int64_t)threadIdx.x * kScanItems + i;
-    if (j < n) {
-      if (ts.v[i]) {
-        lmap[j] = ts.ex[i];
-        gmap[ts.ex[i]] = lo + j;
-      } else {
-        lmap[j] = -1;
-      }
-    }
-  }
-}
-
-__global__ void k_make_keys(int64_t nnz, const int64_t* __restrict__ rgid,
-                            const int64_t* __restrict__ cgid, int64_t rlo, int64_t clo,
-                            const int32_t* __restrict__ lmap_r, const int32_t* __restrict__ lmap_c,
-                            int bits_c, uint64_t* __restrict__ key, int32_t* __restrict__ val) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < nnz;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t lr = (uint32_t)lmap_r[rgid[p] - rlo];
-    const uint64_t lc = (uint32_t)lmap_c[cgid[p] - clo];
-    key[p] = (lr << bits_c) | lc;
-    val[p] = (int32_t)p;
-  }
-}
-
-// Keys of the column-major view from the row-major slots: (lc << bits_r) | lr,
-// value = row-major slot.
-__global__ void k_make_keys_t(int64_t nnz, const uint64_t* __restrict__ skey, int bits_c,
-                              int bits_r, uint64_t* __restrict__ key, int32_t* __restrict__ val) {
-  const uint64_t cmask = bits_c ? ((1ull << bits_c) - 1ull) : 0ull;
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < nnz;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t k = skey[p];
-    key[p] = ((k & cmask) << bits_r) | (k >> bits_c);
-    val[p] = (int32_t)p;
+  for (int i = 0; i < kCompactWords; ++i) {   // words past the range hold no ids
+    const uint64_t bits = __shfl(mine.bits, i);
+    const int rank = __shfl(mine.before, i) + __popcll(bits & ((1ull << lane) - 1ull));
+    const int64_t id = (w0 + i) * 64 + lane;
+    const bool on = (bits >> lane) & 1ull;
+    if (id < ax.range) ax.lmap[id] = on ? rank : -1;
+    if (on) ax.gmap[rank] = ax.lo + id;
   }
 }
 
 // ---------------------------------------------------------- radix sort
+//
+// One pass: a histogram per tile (counts[tile][digit]), a scan of each digit's
+// counts with the digit's total, and a stable scatter.  Consecutive tiles run
+// on one XCD, where the ends of their neighbouring runs meet in one L2 line.
+// Per pass, us before and after (block barriers in each of the eight ranking
+// rounds, counts[digit][tile] written and scanned by three kernels): 4.1M
+// entries scatter 40 to 23, histogram 11 to 8, scans 16 to 6; 31.4M entries
+// scatter 278 to 180 (tiles of 2048 there: 202), histogram 84 to 51.  What bounds a pass is
+// the scatter's traffic (24 bytes an entry) and, below some millions of
+// entries, how few tiles there are; tiles of 2048 entries serve smaller inputs
+// and tiles of 4096, whose digits' runs are 16 entries (128 bytes of keys) on
+// average, larger ones.
 
 constexpr int kSortThreads = 256;
-constexpr int kSortRounds = 8;
-constexpr int kSortTile = kSortThreads * kSortRounds;   // 2048 keys per block
+constexpr int64_t kSortLarge = int64_t(6) << 20;   // entries from which tiles are large
 
-__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint64_t* __restrict__ key,
-                                                             int64_t n, int shift, int64_t nblk,
-                                                             int32_t* __restrict__ counts) {
-  __shared__ int hist[256];
-  hist[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-#pragma unroll
-  for (int r = 0; r < kSortRounds; ++r) {
-    int64_t j = base + r * kSortThreads + threadIdx.x;
-    if (j < n) atomicAdd(&hist[(key[j] >> shift) & 255], 1);
-  }
-  __syncthreads();
-  counts[(int64_t)threadIdx.x * nblk + blockIdx.x] = hist[threadIdx.x];
+inline int64_t sort_tiles(int64_t n) {
+  const int64_t tile = n < kSortLarge ? 2048 : 4096;
+  return (n + tile - 1) / tile;
 }
 
-// Stable scatter of one tile of kSortTile keys.  Items are ranked in rounds
-// of 256 (item r*256 + t of the tile), so the rank of an item among equal
-// digits follows tile order.  Each item is first placed in LDS at its
-// position inside the tile's digit-ordered sequence; the tile is then
-// written out in that order, so consecutive threads store consecutive
-// elements of one digit's run instead of one element per cache line.
+// Adds this thread's digits to a tile's histogram (one copy per wavefront).
+struct TileHist {
+  int h[kSortThreads / 64][256];
+};
+
+__device__ inline void hist_clear(TileHist& th) {
+#pragma unroll
+  for (int w = 0; w < kSortThreads / 64; ++w) th.h[w][threadIdx.x] = 0;
+  __syncthreads();
+}
+
+__device__ inline void hist_write(TileHist& th, int64_t tile, int32_t* __restrict__ counts) {
+  __syncthreads();
+  int s = 0;
+#pragma unroll
+  for (int w = 0; w < kSortThreads / 64; ++w) s += th.h[w][threadIdx.x];
+  counts[tile * 256 + threadIdx.x] = s;
+}
+
+template <int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint64_t* __restrict__ key,
+                                                             int64_t n, int shift,
+                                                             int32_t* __restrict__ counts) {
+  __shared__ TileHist th;
+  const int64_t tile = xcd_block(gridDim.x);
+  const int64_t base = tile * (kSortThreads * ITEMS) + threadIdx.x;
+  uint64_t k[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t j = base + r * kSortThreads;
+    k[r] = j < n ? key[j] : 0;
+  }
+  hist_clear(th);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r)
+    if (base + r * kSortThreads < n)
+      atomicAdd(&th.h[threadIdx.x >> 6][(int)(k[r] >> shift) & 255], 1);
+  hist_write(th, tile, counts);
+}
+
+// Keys and the first pass' histogram.  A local id comes from the rank words,
+// or from localMap where the axis was regrouped.
+template <int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_make_keys(
+    int64_t nnz, const int64_t* __restrict__ rgid, const int64_t* __restrict__ cgid, int64_t rlo,
+    int64_t clo, const RankWord* __restrict__ word_r, const RankWord* __restrict__ word_c,
+    const int32_t* __restrict__ lmap_r, const int32_t* __restrict__ lmap_c, int bits_c,
+    uint64_t* __restrict__ key, int32_t* __restrict__ val, int32_t* __restrict__ counts) {
+  __shared__ TileHist th;
+  constexpr int U = 4;   // entries of a thread in flight
+  const int64_t tile = xcd_block(gridDim.x);
+  const int64_t base = tile * (kSortThreads * ITEMS) + threadIdx.x;
+  hist_clear(th);
+#pragma unroll 1
+  for (int r0 = 0; r0 < ITEMS; r0 += U) {
+    int64_t gr[U], gc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = base + (r0 + u) * kSortThreads;
+      gr[u] = p < nnz ? __builtin_nontemporal_load(rgid + p) - rlo : 0;
+      gc[u] = p < nnz ? __builtin_nontemporal_load(cgid + p) - clo : 0;
+    }
+    uint32_t lr[U], lc[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      lr[u] = (uint32_t)(lmap_r ? lmap_r[gr[u]] : rank_of(word_r, gr[u]));
+      lc[u] = (uint32_t)(lmap_c ? lmap_c[gc[u]] : rank_of(word_c, gc[u]));
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = base + (r0 + u) * kSortThreads;
+      if (p < nnz) {
+        const uint64_t k = ((uint64_t)lr[u] << bits_c) | lc[u];
+        key[p] = k;
+        val[p] = (int32_t)p;
+        atomicAdd(&th.h[threadIdx.x >> 6][(int)k & 255], 1);
+      }
+    }
+  }
+  hist_write(th, tile, counts);
+}
+
+// Keys of the column-major view from the row-major slots, (lc << bits_r) | lr,
+// value = row-major slot, and the histogram of the column's lowest digit.
+template <int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_make_keys_t(
+    int64_t nnz, const uint64_t* __restrict__ skey, int bits_c, int bits_r,
+    uint64_t* __restrict__ key, int32_t* __restrict__ val, int32_t* __restrict__ counts) {
+  __shared__ TileHist th;
+  const uint64_t cmask = bits_c ? ((1ull << bits_c) - 1ull) : 0ull;
+  const int64_t tile = xcd_block(gridDim.x);
+  const int64_t base = tile * (kSortThreads * ITEMS) + threadIdx.x;
+  uint64_t k[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t j = base + r * kSortThreads;
+    k[r] = j < nnz ? skey[j] : 0;
+  }
+  hist_clear(th);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t j = base + r * kSortThreads;
+    if (j < nnz) {
+      key[j] = ((k[r] & cmask) << bits_r) | (k[r] >> bits_c);
+      val[j] = (int32_t)j;
+      atomicAdd(&th.h[threadIdx.x >> 6][(int)(k[r] & cmask) & 255], 1);
+    }
+  }
+  hist_write(th, tile, counts);
+}
+
+// Exclusive scan of four digits' counts over the tiles, in place, and their
+// totals.  Thread t takes digit t % 4 of kScanRows consecutive tiles, so a
+// block covers 2048 tiles per round and reads 16 bytes of each.
+constexpr int kScanRows = 8;
+__global__ __launch_bounds__(1024) void k_scan_digits(int32_t* __restrict__ counts, int64_t nblk,
+                                                      int32_t* __restrict__ total) {
+  __shared__ int wsum[16][4];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6, j = t & 3;
+  const int d = blockIdx.x * 4 + j;
+  int carry = 0;
+  for (int64_t base = 0; base < nblk; base += 256 * kScanRows) {
+    const int64_t row = base + (int64_t)(t >> 2) * kScanRows;
+    int v[kScanRows], sum = 0;
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) {
+      v[i] = row + i < nblk ? counts[(row + i) * 256 + d] : 0;
+      sum += v[i];
+    }
+    int inc = sum;   // over the lanes of this digit
+#pragma unroll
+    for (int s = 4; s < 64; s <<= 1) {
+      const int o = __shfl_up(inc, s, 64);
+      if (lane >= s) inc += o;
+    }
+    if (lane >= 60) wsum[w][j] = inc;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int x = wsum[i][j];
+      before += i < w ? x : 0;
+      all += x;
+    }
+    __syncthreads();
+    int ex = carry + before + inc - sum;
+#pragma unroll
+    for (int i = 0; i < kScanRows; ++i) {
+      if (row + i < nblk) counts[(row + i) * 256 + d] = ex;
+      ex += v[i];
+    }
+    carry += all;
+  }
+  if (t < 4) total[d] = carry;
+}
+
+// Stable scatter of one tile.  A wavefront owns ITEMS * 64 consecutive
+// entries and ranks them in rounds of 64 against its own digit counters
+// (ballots give a lane's rank among the round's equal digits), so only the
+// merge of the wavefronts' counters needs the block's barriers.  The tile is
+// then put in digit order in LDS and written out in that order: consecutive
+// threads store consecutive entries of one digit's run.
+template <int ITEMS>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(
     const uint64_t* __restrict__ kin, const int32_t* __restrict__ vin, int64_t n, int shift,
-    int64_t nblk, const int32_t* __restrict__ offsets, uint64_t* __restrict__ kout,
-    int32_t* __restrict__ vout) {
-  __shared__ uint64_t s_key[kSortTile];
-  __shared__ int32_t s_val[kSortTile];
-  __shared__ int start[256];   // first position of each digit inside the tile
-  __shared__ int cnt[256];     // items of each digit in the tile
-  __shared__ int base[256];    // next free position of each digit (advances per round)
-  __shared__ int wcnt[kSortThreads / 64][256];
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ total,
+    uint64_t* __restrict__ kout, int32_t* __restrict__ vout) {
+  constexpr int TILE = kSortThreads * ITEMS;
+  constexpr int NW = kSortThreads / 64;
+  __shared__ uint64_t s_key[TILE];
+  __shared__ int32_t s_val[TILE];
+  __shared__ int cnt[NW][256];     // per wavefront: count, then first position
+  __shared__ int64_t dest[256];    // global position of a digit's run minus its tile position
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int64_t tile = (int64_t)blockIdx.x * kSortTile;
-  uint64_t k[kSortRounds];
-  int32_t v[kSortRounds];
-  cnt[t] = 0;
-  for (int i = 0; i < kSortThreads / 64; ++i) wcnt[i][t] = 0;
-  __syncthreads();
+  const int64_t tile = xcd_block(gridDim.x);
+  const int64_t mine = tile * TILE + w * (ITEMS * 64) + lane;
+  uint64_t k[ITEMS];
+  int32_t v[ITEMS];
 #pragma unroll
-  for (int r = 0; r < kSortRounds; ++r) {
-    const int64_t j = tile + r * kSortThreads + t;
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t j = mine + r * 64;
     k[r] = j < n ? kin[j] : 0;
     v[r] = j < n ? vin[j] : 0;
-    if (j < n) atomicAdd(&cnt[(int)((k[r] >> shift) & 255)], 1);
   }
-  __syncthreads();
-  int total;
-  const int st = block_exclusive_sum<kSortThreads>(cnt[t], &total);
-  start[t] = st;
-  base[t] = st;
-  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW; ++i) cnt[i][t] = 0;
+  const int64_t off = offsets[tile * 256 + t];
+  int tot;
+  const int64_t first = block_exclusive_sum<kSortThreads>(total[t], &tot);   // has barriers
+  int rank[ITEMS];
+  volatile int* my = cnt[w];   // touched by this wavefront alone until the barrier
   const uint64_t lt = (1ull << lane) - 1ull;
 #pragma unroll
-  for (int r = 0; r < kSortRounds; ++r) {
-    const int64_t j = tile + r * kSortThreads + t;
-    const bool valid = j < n;
-    const int d = (int)((k[r] >> shift) & 255);
+  for (int r = 0; r < ITEMS; ++r) {
+    const bool valid = mine + r * 64 < n;
+    const int d = (int)(k[r] >> shift) & 255;
     uint64_t peers = __ballot(valid);
 #pragma unroll
     for (int bit = 0; bit < 8; ++bit) {
       const uint64_t bb = __ballot((d >> bit) & 1);
       peers &= ((d >> bit) & 1) ? bb : ~bb;
     }
-    const int rank = __popcll(peers & lt);
-    if (valid && rank == 0) wcnt[w][d] = __popcll(peers);
-    __syncthreads();
-    if (valid) {
-      int pos = base[d] + rank;
-      for (int i = 0; i < w; ++i) pos += wcnt[i][d];
+    const int below = __popcll(peers & lt);
+    const int seen = my[d];
+    rank[r] = seen + below;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && below == 0) my[d] = seen + __popcll(peers);
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  int sum = 0, part[NW];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    part[i] = sum;
+    sum += cnt[i][t];
+  }
+  int items;
+  const int start = block_exclusive_sum<kSortThreads>(sum, &items);
+#pragma unroll
+  for (int i = 0; i < NW; ++i) cnt[i][t] = start + part[i];
+  dest[t] = first + off - start;
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    if (mine + r * 64 < n) {
+      const int pos = cnt[w][(int)(k[r] >> shift) & 255] + rank[r];
       s_key[pos] = k[r];
       s_val[pos] = v[r];
     }
-    __syncthreads();
-    int add = 0;
-    for (int i = 0; i < kSortThreads / 64; ++i) {
-      add += wcnt[i][t];
-      wcnt[i][t] = 0;
-    }
-    base[t] += add;
-    __syncthreads();
   }
-  // positions [0, total) of the tile now hold its items in (digit, tile order)
-  for (int i = t; i < total; i += kSortThreads) {
-    const uint64_t key = s_key[i];
-    const int d = (int)((key >> shift) & 255);
-    const int within = i - start[d];
-    if (within < 0 || within >= cnt[d]) continue;   // cannot happen; keeps stores in range
-    const int64_t g = (int64_t)offsets[(int64_t)d * nblk + blockIdx.x] + within;
-    if (g < n) {
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int i = r * kSortThreads + t;
+    if (i < items) {
+      const uint64_t key = s_key[i];
+      const int64_t g = dest[(int)(key >> shift) & 255] + i;
       kout[g] = key;
       vout[g] = s_val[i];
     }
@@ -371,30 +545,61 @@ __global__ __launch_bounds__(256) void k_build_slots(int64_t nnz, int64_t nrows,
 
 // ------------------------------------------------------- CSR input
 
-// rows[p] = lo + i for the entries p in [rowptr[i], rowptr[i+1]) (binary
-// search per entry; a non-monotone rowptr only raises *err, every id stays in
-// the range).
-__global__ void k_csr_rows(int64_t n, const int64_t* __restrict__ rowptr, int64_t nnz, int64_t lo,
-                           int64_t* __restrict__ rows) {
-  for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < nnz;
-       p += (int64_t)gridDim.x * blockDim.x) {
-    int64_t a = 0, b = n;   // largest i in [0, n) with rowptr[i] <= p
-    while (b - a > 1) {
-      const int64_t m = (a + b) >> 1;
-      if (rowptr[m] <= p) a = m; else b = m;
-    }
-    rows[p] = lo + a;
-  }
-}
+constexpr int kCsrChunk = 512;   // entries of a wavefront of k_csr_rows
 
-__global__ void k_csr_check(int64_t n, const int64_t* __restrict__ rowptr, int64_t nnz,
+// Checks the row pointer, flags the rows with entries and notes the row of
+// every kCsrChunk-th entry.
+__global__ void k_csr_flags(int64_t n, const int64_t* __restrict__ rowptr, int64_t nnz,
+                            uint8_t* __restrict__ flag, int32_t* __restrict__ chunk_row,
                             int32_t* __restrict__ err) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const int64_t v = rowptr[i];
-    if ((i == 0 && v != 0) || (i == n && v != nnz) || (i < n && rowptr[i + 1] < v) || v < 0 ||
-        v > nnz)
-      err[0] = 1;
+    const int64_t next = i < n ? rowptr[i + 1] : v;
+    const bool bad = (i == 0 && v != 0) || (i == n && v != nnz) || next < v || v < 0 || v > nnz;
+    if (bad) err[0] = 1;
+    if (i < n) {
+      flag[i] = next > v;
+      if (!bad && next <= nnz)
+        for (int64_t c = (v + kCsrChunk - 1) / kCsrChunk; c * kCsrChunk < next; ++c)
+          chunk_row[c] = (int32_t)i;
+    }
+  }
+}
+
+// rows[p] = lo + i for the entries p in [rowptr[i], rowptr[i+1]): each entry's
+// row is searched between the rows of its chunk's ends, all of a lane's
+// entries in step.  (With a bad row pointer, which is reported, chunk_row may
+// hold anything: the rows found still lie in the range.)
+__global__ __launch_bounds__(256) void k_csr_rows(int64_t n, const int64_t* __restrict__ rowptr,
+                                                  int64_t nnz, int64_t lo,
+                                                  const int32_t* __restrict__ chunk_row,
+                                                  int64_t* __restrict__ rows) {
+  constexpr int U = kCsrChunk / 64;
+  const int lane = threadIdx.x & 63;
+  const int64_t w = blockIdx.x * (int64_t)4 + (threadIdx.x >> 6);
+  const int64_t p0 = w * kCsrChunk;
+  if (p0 >= nnz) return;
+  int64_t a = chunk_row[w], b = p0 + kCsrChunk < nnz ? chunk_row[w + 1] : n - 1;
+  a = a < 0 ? 0 : a >= n ? n - 1 : a;
+  b = b < a ? a : b >= n ? n - 1 : b;
+  int64_t x[U], y[U];   // the row lies in [x, y)
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    x[u] = a;
+    y[u] = b + 1;
+  }
+  for (int64_t span = b + 1 - a; span > 1; span = (span + 1) >> 1) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t m = (x[u] + y[u]) >> 1;   // x itself once y == x + 1
+      if (rowptr[m] <= p0 + u * 64 + lane) x[u] = m; else y[u] = m;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t p = p0 + u * 64 + lane;
+    if (p < nnz) rows[p] = lo + x[u];
   }
 }
 
@@ -487,9 +692,8 @@ struct Bump {
 struct Layout {
   size_t gmap_r, gmap_c, lmap_r, lmap_c, rowptr, colidx, perm, head, tile_row;
   size_t colptr, rowidx_t, slot_t, head_t, tile_col, small, goff_r, goff_c;
-  size_t keys0, keys1, vals0, vals1, counts, partial;
+  size_t keys0, keys1, vals0, vals1, counts, digits, word_r, word_c, partial_r, partial_c;
   size_t total;
-  int64_t sort_blocks, partial_len;
 };
 
 Layout make_layout(int64_t nnz, int64_t rr, int64_t cr, uint32_t flags) {
@@ -519,67 +723,72 @@ Layout make_layout(int64_t nnz, int64_t rr, int64_t cr, uint32_t flags) {
   L.goff_r = b.take(4 * (size_t)(kMaxGroups + 1));
   L.goff_c = b.take(4 * (size_t)(kMaxGroups + 1));
   // temporaries (dead after plan creation)
-  L.sort_blocks = (nnz + kSortTile - 1) / kSortTile;
   L.keys0 = b.take(8 * (size_t)nnz);
   L.keys1 = b.take(8 * (size_t)nnz);
   L.vals0 = b.take(4 * (size_t)nnz);
   L.vals1 = b.take(4 * (size_t)nnz);
-  L.counts = b.take(4 * (size_t)(256 * L.sort_blocks));
-  int64_t scan_max = rr > cr ? rr : cr;
-  if (256 * L.sort_blocks > scan_max) scan_max = 256 * L.sort_blocks;
-  L.partial_len = (scan_max + kScanTile - 1) / kScanTile + 1;
-  L.partial = b.take(4 * (size_t)L.partial_len);
+  L.counts = b.take(4 * (size_t)(256 * ((nnz + 2047) / 2048)));   // tiles of either size
+  L.digits = b.take(4 * 256);
+  L.word_r = b.take(sizeof(RankWord) * (size_t)((rr + 63) / 64));
+  L.word_c = b.take(sizeof(RankWord) * (size_t)((cr + 63) / 64));
+  L.partial_r = b.take(4 * (size_t)((rr + kWordTile - 1) / kWordTile));
+  L.partial_c = b.take(4 * (size_t)((cr + kWordTile - 1) / kWordTile));
   L.total = b.off;
   return L;
 }
 
-spc3d_status scan_exclusive(int32_t* data, int64_t n, int32_t* partial, int32_t* total,
-                            hipStream_t s) {
-  if (n <= 0) return SPC3D_OK;
-  const int64_t nb = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n,
-                     partial);
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partial, nb, total);
-  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanThreads), 0, s, data, n,
-                     partial, data);
-  SPC3D_LAUNCHED("scan");
-  return SPC3D_OK;
-}
-
-// Localize one axis: flags -> lmap, gmap; the count lands in *d_count.
-spc3d_status localize(int64_t nnz, const int64_t* gid, int64_t lo, int64_t range, int32_t* lmap,
-                      int64_t* gmap, int32_t* partial, int32_t* d_count, int32_t* d_err,
-                      hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(range, 256)), dim3(256), 0, s, lmap, range, 0);
+// Localize both axes: flags -> words -> localMap, globalMap and the counts.
+// rowptr: the block is in CSR (the row axis has no ids to mark).
+spc3d_status localize(int64_t nnz, const Axis& r, const Axis& c, const int64_t* rowptr,
+                      int32_t* chunk_row, int32_t* d_err, int32_t* d_csr_err, hipStream_t s) {
+  const int64_t most = r.range > c.range ? r.range : c.range;
+  hipLaunchKernelGGL(k_clear_flags, dim3(grid_for((most + 15) / 16, 256, 4096), 2), dim3(256), 0, s,
+                     r, c);
+  if (rowptr)
+    hipLaunchKernelGGL(k_csr_flags, dim3(grid_for(r.range + 1, 256)), dim3(256), 0, s, r.range,
+                       rowptr, nnz, r.flag, chunk_row, d_csr_err);
   if (nnz > 0)
-    hipLaunchKernelGGL(k_mark, dim3(grid_for(nnz, 256)), dim3(256), 0, s, nnz, gid, lo,
-                       lo + range, lmap, d_err);
-  const int64_t nb = (range + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanThreads), 0, s, lmap, range,
-                     partial);
-  hipLaunchKernelGGL(k_scan_partials, dim3(1), dim3(1024), 0, s, partial, nb, d_count);
-  hipLaunchKernelGGL(k_compact, dim3((unsigned)nb), dim3(kScanThreads), 0, s, lmap, range, lo,
-                     partial, gmap);
+    hipLaunchKernelGGL(k_mark, dim3(grid_for(nnz, 1024, INT32_MAX), 2), dim3(256), 0, s, nnz, r, c,
+                       d_err);
+  hipLaunchKernelGGL(k_rank_words, dim3(grid_for(most, kWordTile, INT32_MAX), 2), dim3(256), 0, s,
+                     r, c);
+  hipLaunchKernelGGL(k_scan_partials, dim3(2), dim3(1024), 0, s, r, c);
+  hipLaunchKernelGGL(k_compact, dim3(grid_for((most + 63) / 64, 4 * kCompactWords, INT32_MAX), 2),
+                     dim3(256), 0, s, r, c);
   SPC3D_LAUNCHED("localize");
   return SPC3D_OK;
 }
 
-// Stable LSD sort of (key, val) over the low `bits` bits.  The result ends in
-// (k0, v0) or (k1, v1); *out_k / *out_v point at it.
-spc3d_status radix_sort(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1, int64_t n,
-                        int bits, int32_t* counts, int64_t nblk, int32_t* partial,
+// The sort's scratch.
+struct SortTemp {
+  uint64_t *k0, *k1;
+  int32_t *v0, *v1, *counts, *digits;
+};
+
+// Stable LSD sort of (t.k0, t.v0) over bits [from, to).  counted: the first
+// digit's histogram is in t.counts already.  *out_k / *out_v point at the
+// result, the other pair is free.
+spc3d_status radix_sort(const SortTemp& t, int64_t n, int from, int to, bool counted,
                         hipStream_t s, uint64_t** out_k, int32_t** out_v) {
-  uint64_t* ks = k0;
-  int32_t* vs = v0;
-  uint64_t* kd = k1;
-  int32_t* vd = v1;
-  for (int shift = 0; shift < bits; shift += 8) {
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)nblk), dim3(kSortThreads), 0, s, ks, n,
-                       shift, nblk, counts);
-    spc3d_status st = scan_exclusive(counts, 256 * nblk, partial, nullptr, s);
-    if (st != SPC3D_OK) return st;
-    hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)nblk), dim3(kSortThreads), 0, s, ks, vs,
-                       n, shift, nblk, counts, kd, vd);
+  uint64_t *ks = t.k0, *kd = t.k1;
+  int32_t *vs = t.v0, *vd = t.v1;
+  const int64_t nblk = sort_tiles(n);
+  const dim3 grid((unsigned)nblk), block(kSortThreads);
+  const bool small = n < kSortLarge;
+  for (int shift = from; shift < to; shift += 8) {
+    if (!(counted && shift == from)) {
+      if (small)
+        hipLaunchKernelGGL(k_radix_hist<8>, grid, block, 0, s, ks, n, shift, t.counts);
+      else
+        hipLaunchKernelGGL(k_radix_hist<16>, grid, block, 0, s, ks, n, shift, t.counts);
+    }
+    hipLaunchKernelGGL(k_scan_digits, dim3(64), dim3(1024), 0, s, t.counts, nblk, t.digits);
+    if (small)
+      hipLaunchKernelGGL(k_radix_scatter<8>, grid, block, 0, s, ks, vs, n, shift, t.counts,
+                         t.digits, kd, vd);
+    else
+      hipLaunchKernelGGL(k_radix_scatter<16>, grid, block, 0, s, ks, vs, n, shift, t.counts,
+                         t.digits, kd, vd);
     SPC3D_LAUNCHED("radix pass");
     uint64_t* tk = ks; ks = kd; kd = tk;
     int32_t* tv = vs; vs = vd; vd = tv;
@@ -591,18 +800,15 @@ spc3d_status radix_sort(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1, in
 
 // Re-assigns the local ids of one axis in (group, id) order (see above).
 spc3d_status group_axis(int64_t n, int64_t lo, int64_t* gmap, int32_t* lmap,
-                        const int32_t* group, int32_t ngroups, int32_t* goff, uint64_t* k0,
-                        int32_t* v0, uint64_t* k1, int32_t* v1, int32_t* counts,
-                        int32_t* partial, int32_t* d_err, hipStream_t s) {
+                        const int32_t* group, int32_t ngroups, int32_t* goff, const SortTemp& t,
+                        int32_t* d_err, hipStream_t s) {
   if (n > 0) {
     hipLaunchKernelGGL(k_group_keys, dim3(grid_for(n, 256)), dim3(256), 0, s, n, gmap, lo, group,
-                       ngroups, k0, v0, d_err);
+                       ngroups, t.k0, t.v0, d_err);
     SPC3D_LAUNCHED("group keys");
     uint64_t* sk;
     int32_t* sv;
-    const int64_t nblk = (n + kSortTile - 1) / kSortTile;
-    spc3d_status st = radix_sort(k0, v0, k1, v1, n, ceil_log2(ngroups), counts, nblk, partial,
-                                 s, &sk, &sv);
+    spc3d_status st = radix_sort(t, n, 0, ceil_log2(ngroups), false, s, &sk, &sv);
     if (st != SPC3D_OK) return st;
     hipLaunchKernelGGL(k_apply_order, dim3(grid_for(n, 256)), dim3(256), 0, s, n, sv, lo, gmap,
                        lmap);
@@ -697,12 +903,12 @@ spc3d_status create_plan(spc3d_plan* out, int64_t nnz, const int64_t* d_row_gid,
     p->tile_col = reinterpret_cast<int32_t*>(w + L.tile_col);
   }
   int32_t* small = reinterpret_cast<int32_t*>(w + L.small);
-  uint64_t* keys0 = reinterpret_cast<uint64_t*>(w + L.keys0);
-  uint64_t* keys1 = reinterpret_cast<uint64_t*>(w + L.keys1);
-  int32_t* vals0 = reinterpret_cast<int32_t*>(w + L.vals0);
-  int32_t* vals1 = reinterpret_cast<int32_t*>(w + L.vals1);
-  int32_t* counts = reinterpret_cast<int32_t*>(w + L.counts);
-  int32_t* partial = reinterpret_cast<int32_t*>(w + L.partial);
+  const SortTemp tmp{reinterpret_cast<uint64_t*>(w + L.keys0),
+                     reinterpret_cast<uint64_t*>(w + L.keys1),
+                     reinterpret_cast<int32_t*>(w + L.vals0),
+                     reinterpret_cast<int32_t*>(w + L.vals1),
+                     reinterpret_cast<int32_t*>(w + L.counts),
+                     reinterpret_cast<int32_t*>(w + L.digits)};
   if (d_group_r) {
     p->ngroups_r = ngroups_r;
     p->goff_r = reinterpret_cast<int32_t*>(w + L.goff_r);
@@ -717,25 +923,25 @@ spc3d_status create_plan(spc3d_plan* out, int64_t nnz, const int64_t* d_row_gid,
     return s;
   };
   hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, stream, small, (int64_t)64, 0);
-  if (d_rowptr) {
-    // CSR input: check the row pointer, expand it to one row id per entry in
-    // the colidx / perm region (free until the slots are built)
-    hipLaunchKernelGGL(k_csr_check, dim3(grid_for(rr + 1, 256)), dim3(256), 0, stream, rr,
-                       d_rowptr, nnz, small + 4);
-    if (nnz > 0) {
-      int64_t* rows_tmp = reinterpret_cast<int64_t*>(w + L.colidx);
-      hipLaunchKernelGGL(k_csr_rows, dim3(grid_for(nnz, 256)), dim3(256), 0, stream, rr, d_rowptr,
-                         nnz, row_lo, rows_tmp);
-      d_row_gid = rows_tmp;
-    }
+  const Axis ax_r{d_rowptr ? nullptr : d_row_gid, row_lo, rr,
+                  reinterpret_cast<uint8_t*>(p->lmap_r),
+                  reinterpret_cast<RankWord*>(w + L.word_r),
+                  reinterpret_cast<int32_t*>(w + L.partial_r), p->lmap_r, p->gmap_r, small + 0};
+  const Axis ax_c{d_col_gid, col_lo, cr, reinterpret_cast<uint8_t*>(p->lmap_c),
+                  reinterpret_cast<RankWord*>(w + L.word_c),
+                  reinterpret_cast<int32_t*>(w + L.partial_c), p->lmap_c, p->gmap_c, small + 1};
+  int32_t* chunk_row = tmp.counts;   // free until the sort
+  st = localize(nnz, ax_r, ax_c, d_rowptr, chunk_row, small + 2, small + 4, stream);
+  if (st != SPC3D_OK) return bail(st);
+  if (d_rowptr && nnz > 0) {
+    // CSR input: expand the row pointer to one row id per entry in the colidx
+    // / perm region (free until the slots are built)
+    int64_t* rows_tmp = reinterpret_cast<int64_t*>(w + L.colidx);
+    hipLaunchKernelGGL(k_csr_rows, dim3(grid_for(nnz, 4 * kCsrChunk, INT32_MAX)), dim3(256), 0, stream, rr,
+                       d_rowptr, nnz, row_lo, chunk_row, rows_tmp);
     SPC3D_LAUNCHED("csr rows");
+    d_row_gid = rows_tmp;
   }
-  st = localize(nnz, d_row_gid, row_lo, rr, p->lmap_r, p->gmap_r, partial, small + 0,
-                small + 2, stream);
-  if (st != SPC3D_OK) return bail(st);
-  st = localize(nnz, d_col_gid, col_lo, cr, p->lmap_c, p->gmap_c, partial, small + 1,
-                small + 2, stream);
-  if (st != SPC3D_OK) return bail(st);
   int32_t host_small[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   hipError_t e = hipMemcpyAsync(host_small, small, sizeof host_small, hipMemcpyDeviceToHost,
                                 stream);
@@ -750,13 +956,13 @@ spc3d_status create_plan(spc3d_plan* out, int64_t nnz, const int64_t* d_row_gid,
   p->C = host_small[1];
   if (d_group_r || d_group_c) {
     if (d_group_r) {
-      st = group_axis(p->R, row_lo, p->gmap_r, p->lmap_r, d_group_r, ngroups_r, p->goff_r, keys0,
-                      vals0, keys1, vals1, counts, partial, small + 3, stream);
+      st = group_axis(p->R, row_lo, p->gmap_r, p->lmap_r, d_group_r, ngroups_r, p->goff_r, tmp,
+                      small + 3, stream);
       if (st != SPC3D_OK) return bail(st);
     }
     if (d_group_c) {
-      st = group_axis(p->C, col_lo, p->gmap_c, p->lmap_c, d_group_c, ngroups_c, p->goff_c, keys0,
-                      vals0, keys1, vals1, counts, partial, small + 3, stream);
+      st = group_axis(p->C, col_lo, p->gmap_c, p->lmap_c, d_group_c, ngroups_c, p->goff_c, tmp,
+                      small + 3, stream);
       if (st != SPC3D_OK) return bail(st);
     }
     int32_t host_err = 0;
@@ -768,31 +974,46 @@ spc3d_status create_plan(spc3d_plan* out, int64_t nnz, const int64_t* d_row_gid,
 
   const int bits_r = ceil_log2(p->R), bits_c = ceil_log2(p->C);
   if (nnz > 0) {
-    hipLaunchKernelGGL(k_make_keys, dim3(grid_for(nnz, 256)), dim3(256), 0, stream, nnz,
-                       d_row_gid, d_col_gid, row_lo, col_lo, p->lmap_r, p->lmap_c, bits_c, keys0,
-                       vals0);
+    const int64_t nblk = sort_tiles(nnz);
+    const dim3 tiles((unsigned)nblk), threads(kSortThreads);
+    const bool small_sort = nnz < kSortLarge;
+    const int32_t* map_r = d_group_r ? p->lmap_r : nullptr;
+    const int32_t* map_c = d_group_c ? p->lmap_c : nullptr;
+    if (small_sort)
+      hipLaunchKernelGGL(k_make_keys<8>, tiles, threads, 0, stream, nnz, d_row_gid, d_col_gid,
+                         row_lo, col_lo, ax_r.word, ax_c.word, map_r, map_c, bits_c, tmp.k0, tmp.v0,
+                         tmp.counts);
+    else
+      hipLaunchKernelGGL(k_make_keys<16>, tiles, threads, 0, stream, nnz, d_row_gid, d_col_gid,
+                         row_lo, col_lo, ax_r.word, ax_c.word, map_r, map_c, bits_c, tmp.k0, tmp.v0,
+                         tmp.counts);
     SPC3D_LAUNCHED("make_keys");
     uint64_t* sk;
     int32_t* sv;
-    st = radix_sort(keys0, vals0, keys1, vals1, nnz, bits_r + bits_c, counts, L.sort_blocks,
-                    partial, stream, &sk, &sv);
+    st = radix_sort(tmp, nnz, 0, bits_r + bits_c, true, stream, &sk, &sv);
     if (st != SPC3D_OK) return bail(st);
     hipLaunchKernelGGL(k_build_slots, dim3(grid_for(nnz, 256, INT32_MAX)), dim3(256), 0, stream,
                        nnz, p->R, sk, sv, bits_c, p->colidx, p->perm, p->rowptr, p->head,
                        p->tile_row);
     SPC3D_LAUNCHED("build_slots");
     if (flags & SPC3D_BUILD_CSC) {
-      uint64_t* tk = (sk == keys0) ? keys1 : keys0;
-      int32_t* tv = (sv == vals0) ? vals1 : vals0;
-      hipLaunchKernelGGL(k_make_keys_t, dim3(grid_for(nnz, 256)), dim3(256), 0, stream, nnz, sk,
-                         bits_c, bits_r, tk, tv);
+      SortTemp t = tmp;   // the sorted keys are read, the other pair written
+      if (sk == tmp.k0) {
+        t.k0 = tmp.k1;
+        t.k1 = tmp.k0;
+        t.v0 = tmp.v1;
+        t.v1 = tmp.v0;
+      }
+      if (small_sort)
+        hipLaunchKernelGGL(k_make_keys_t<8>, tiles, threads, 0, stream, nnz, sk, bits_c, bits_r,
+                           t.k0, t.v0, t.counts);
+      else
+        hipLaunchKernelGGL(k_make_keys_t<16>, tiles, threads, 0, stream, nnz, sk, bits_c, bits_r,
+                           t.k0, t.v0, t.counts);
       SPC3D_LAUNCHED("make_keys_t");
-      uint64_t* ok = (tk == keys0) ? keys1 : keys0;
-      int32_t* ov = (tv == vals0) ? vals1 : vals0;
       uint64_t* sk2;
       int32_t* sv2;
-      st = radix_sort(tk, tv, ok, ov, nnz, bits_r + bits_c, counts, L.sort_blocks, partial,
-                      stream, &sk2, &sv2);
+      st = radix_sort(t, nnz, bits_r, bits_r + bits_c, true, stream, &sk2, &sv2);
       if (st != SPC3D_OK) return bail(st);
       hipLaunchKernelGGL(k_build_slots, dim3(grid_for(nnz, 256, INT32_MAX)), dim3(256), 0,
                          stream, nnz, p->C, sk2, sv2, bits_r, p->rowidx_t, p->slot_t, p->colptr,
