@@ -34,13 +34,16 @@
 // order.  All merge orders depend only on the structure, so results are
 // deterministic.
 //
-// What bounds it: vector instructions (about 45 per slot of eight groups) and
-// the row lines that miss L2, about evenly.  Registers decide the rest: 92 for
-// bfloat16 rows of 128 bytes, five wavefronts a SIMD; a second loop body for
-// steps without a row start needed 118 to 156 and was slower (180 to 192
-// against 159 us).  us before and after (MI355X, inference, bfloat16, K = 64):
-// R-MAT 2^18, degree 32 218 to 159, degree 8 91 to 65; 2^16 69 to 54; 2^14,
-// degree 16 48 to 23; FP32 2^16 93 to 73.
+// What bounds it: vector instructions.  At R-MAT 2^18, degree 32, bfloat16,
+// K = 64 it issues 87.6 million (92 per slot of eight groups), 143 of 159 us
+// at four cycles each on 1024 SIMDs and 2.4 GHz; the 790 MB read beyond L2
+// take 121 us at the card's copy rate, underneath.  The count is that of the
+// kernel before; what went is the waiting.  Registers decide how much overlaps:
+// 92 for bfloat16 rows of 128 bytes, five wavefronts a SIMD; a second loop body
+// for steps without a row start needed 118 to 156 and took 180 to 192 us.
+// us before and after (MI355X, inference, bfloat16, K = 64): R-MAT 2^18,
+// degree 32 218 to 159, degree 8 91 to 65; 2^16, degree 32 69 to 54; 2^14,
+// degree 16 48 to 23; FP32 2^16, degree 32 93 to 73.
 #include <cmath>
 
 #include "run.h"
@@ -440,9 +443,10 @@ spc3d_status attn_shape(int32_t kz, spc3d_dtype t, int variant, int64_t nnz, Att
   const int nvec = kz / sh->vec;
   if (variant < 0) {
     sh->lanes = nvec < 16 ? nvec : 16;
-    // Runs of 64 slots, shorter where that leaves under 3500 wavefronts: at
-    // 2^14 vertices, degree 16 (228,000 entries) runs of 64 took 48 us, of 16
-    // take 23.
+    // Runs of 64 slots, shorter where that leaves under 3500 wavefronts.  us for
+    // runs of 16, 32, 64 (bfloat16, K = 64, eight groups): 261,000 entries 18.9,
+    // 25.4, 39.6; 523,000 26.5, 29.0, 42.1; 2.09 million 73.0, 71.1, 70.2; 8.4
+    // million 349, 338, 333.
     const int64_t groups = sh->lanes > 0 ? 64 / sh->lanes : 1;
     sh->lg_s = nnz >= 3500 * 64 * groups ? 6 : nnz >= 3500 * 32 * groups ? 5 : 4;
   } else {
