@@ -124,12 +124,19 @@ def _check(status: int, func: str):
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """The stream's handle; without one, the current stream's of the current
+    device, read as a number (torch.cuda.current_stream() builds an object
+    around it first)."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # the argument types convert the number (lib())
+    return None if t is None else t.data_ptr()
 
 
 def _need(cond: bool, msg: str):
@@ -171,6 +178,7 @@ class Plan:
                "spc3d_plan_query")
         self.R, self.C, self.nnz = R.value, C.value, nnz.value
         self._bufs = {}
+        self._sizes = {}   # scratch sizes asked for: they depend on the block alone
 
     def _view(self, addr, n, dtype):
         if addr is None or n == 0:
@@ -215,6 +223,13 @@ class Plan:
             b = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=self.ws.device)
             self._bufs[key] = b
         return b
+
+    def size(self, key, query):
+        """Bytes of scratch for the calls named by key: query() the first time."""
+        n = self._sizes.get(key)
+        if n is None:
+            n = self._sizes[key] = query()
+        return n
 
     def __del__(self):
         try:
@@ -330,6 +345,19 @@ def spmm_buffer_size(plan: Plan, transpose: int, kz: int, variant: int = -1) -> 
     return b.value
 
 
+def _spmm_buf(plan: Plan, transpose: int, kz: int, variant: int, buf):
+    """The scratch of an SpMM call: the caller's (the C call checks its size),
+    or the plan's own.  An explicit variant is looked at here in either case,
+    since the C call leaves it unread on an empty block."""
+    if buf is not None:
+        if variant >= 0:
+            spmm_buffer_size(plan, transpose, kz, variant)
+        return buf
+    need = plan.size(("spmm", transpose, kz, variant),
+                     lambda: spmm_buffer_size(plan, transpose, kz, variant))
+    return plan.buffer(("spmm", transpose), need)
+
+
 def spmm(plan: Plan, vals, X: torch.Tensor, transpose: int = 0, kz: int | None = None,
          out: torch.Tensor | None = None, mode: int = OVERWRITE, variant: int = -1,
          buf: torch.Tensor | None = None, stream=None):
@@ -344,9 +372,7 @@ def spmm(plan: Plan, vals, X: torch.Tensor, transpose: int = 0, kz: int | None =
         out = torch.empty((n, kz), dtype=torch.float32, device=X.device)
     _need(out.dtype == torch.float32 and out.is_contiguous() and out.numel() >= n * kz
           and _rows_of(out, kz), "out must hold n rows of kz FP32 values")
-    need = spmm_buffer_size(plan, transpose, kz, variant)
-    if buf is None:
-        buf = plan.buffer(("spmm", transpose), need)
+    buf = _spmm_buf(plan, transpose, kz, variant, buf)
     _check(lib().spc3d_spmm(plan.handle, transpose, _ptr(vals), _ptr(X), _dtype_code(X), kz,
                             _ptr(out), mode, variant, _ptr(buf), buf.numel(), _stream(stream)),
            "spc3d_spmm")
@@ -373,9 +399,7 @@ def sddmm_spmm(plan: Plan, vals, A: torch.Tensor, B: torch.Tensor, kz: int | Non
           "out must hold nnz FP32 values")
     _need(Y.dtype == torch.float32 and Y.is_contiguous() and Y.numel() >= plan.R * kz
           and _rows_of(Y, kz), "Y must hold R rows of kz FP32 values")
-    need = spmm_buffer_size(plan, 0, kz, variant)
-    if buf is None:
-        buf = plan.buffer(("spmm", 0), need)
+    buf = _spmm_buf(plan, 0, kz, variant, buf)
     _check(lib().spc3d_sddmm_spmm(plan.handle, _ptr(vals), _ptr(A), _ptr(B), _dtype_code(A), kz,
                                   _ptr(out), _ptr(Y), mode, variant, _ptr(buf), buf.numel(),
                                   _stream(stream)), "spc3d_sddmm_spmm")
@@ -405,9 +429,7 @@ def sddmm_spmm_scatter(plan: Plan, vals, A: torch.Tensor, B: torch.Tensor, dst: 
         out = torch.empty(plan.nnz, dtype=torch.float32, device=A.device)
     _need(out.dtype == torch.float32 and out.is_contiguous() and out.numel() >= plan.nnz,
           "out must hold nnz FP32 values")
-    need = spmm_buffer_size(plan, 0, kz, variant)
-    if buf is None:
-        buf = plan.buffer(("spmm", 0), need)
+    buf = _spmm_buf(plan, 0, kz, variant, buf)
     _check(lib().spc3d_sddmm_spmm_scatter(plan.handle, _ptr(vals), _ptr(A), _ptr(B),
                                           _dtype_code(A), kz, _ptr(out), out_mode, _ptr(dst),
                                           dst.stride(0), k0, variant, _ptr(buf), buf.numel(),
@@ -490,7 +512,7 @@ def row_softmax(plan: Plan, e: torch.Tensor, out=None, stream=None):
     _need(e.dtype == torch.float32 and e.is_contiguous() and e.numel() >= plan.nnz,
           "e must hold nnz FP32 values")
     out = torch.empty_like(e) if out is None else out
-    buf = plan.buffer("softmax", row_softmax_buffer_size(plan))
+    buf = plan.buffer("softmax", plan.size("softmax", lambda: row_softmax_buffer_size(plan)))
     _check(lib().spc3d_row_softmax(plan.handle, _ptr(e), _ptr(out), _ptr(buf), buf.numel(),
                                    _stream(stream)), "spc3d_row_softmax")
     return out
@@ -499,7 +521,7 @@ def row_softmax(plan: Plan, e: torch.Tensor, out=None, stream=None):
 def row_softmax_bwd(plan: Plan, alpha: torch.Tensor, dalpha: torch.Tensor, out=None, stream=None):
     _need(alpha.numel() >= plan.nnz and dalpha.numel() >= plan.nnz, "need nnz values")
     out = torch.empty_like(alpha) if out is None else out
-    buf = plan.buffer("softmax", row_softmax_buffer_size(plan))
+    buf = plan.buffer("softmax", plan.size("softmax", lambda: row_softmax_buffer_size(plan)))
     _check(lib().spc3d_row_softmax_bwd(plan.handle, _ptr(alpha), _ptr(dalpha), _ptr(out),
                                        _ptr(buf), buf.numel(), _stream(stream)),
            "spc3d_row_softmax_bwd")
@@ -559,7 +581,8 @@ def attention_fwd(plan: Plan, Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor,
         _need(stats.dtype == torch.float32 and stats.is_contiguous()
               and stats.numel() >= 2 * plan.R, "stats must hold R (max, sum) pairs")
     dt = _dtype_code(Q)
-    need = attention_fwd_buffer_size(plan, kz, dt, variant)
+    need = plan.size(("attention", kz, dt, variant),
+                     lambda: attention_fwd_buffer_size(plan, kz, dt, variant))
     if buf is None:
         buf = plan.buffer(("attention", kz), need)
     _check(lib().spc3d_attention_fwd(plan.handle, _ptr(Q), _ptr(K), _ptr(V), dt, kz, _ptr(out),
