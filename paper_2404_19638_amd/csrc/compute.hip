@@ -17,6 +17,7 @@ SPC3D_EXTERN_LAUNCHERS(float, 1)
 SPC3D_EXTERN_LAUNCHERS(bf16_t, 8)
 SPC3D_EXTERN_LAUNCHERS(bf16_t, 1)
 #undef SPC3D_EXTERN_LAUNCHERS
+extern template void launch_sddmm_ragged<bf16_t, 8>(SPC3D_SDDMM_LAUNCH_ARGS);
 extern template void launch_run<float, 4, true>(SPC3D_RUN_LAUNCH_ARGS);
 extern template void launch_run<float, 4, false>(SPC3D_RUN_LAUNCH_ARGS);
 extern template void launch_run<bf16_t, 8, true>(SPC3D_RUN_LAUNCH_ARGS);
@@ -272,7 +273,10 @@ spc3d_status spc3d_sddmm(spc3d_plan h, const float* d_vals, const void* d_A, con
   const int64_t nblocks = (nitems + 3) / 4;
   const Orient o = p->csr();
   const int acc = mode == SPC3D_ACCUMULATE;
-  if (ab_t == SPC3D_F32) {
+  if (variant < 0 && pick_ragged(kz, ab_t, d_A, d_B, &sh)) {
+    launch_sddmm_ragged<bf16_t, 8>(sh, stream, p->nnz, nitems, nblocks, o, d_vals, d_A, d_B, kz,
+                                   d_out, acc);
+  } else if (ab_t == SPC3D_F32) {
     if (sh.vec == 4)
       launch_sddmm<float, 4>(sh, stream, p->nnz, nitems, nblocks, o, d_vals, d_A, d_B, kz, d_out,
                              acc);

@@ -117,9 +117,42 @@ __device__ inline float lane_dot(const float (&a)[NCH][VEC], const float (&b)[NC
   return acc;
 }
 
-// ------------------------------------------------------------------ SDDMM
+// Ragged bfloat16 rows (kz even, no multiple of 8, or rows not 16-byte
+// aligned; kz >= 8).  The loads stay 16 bytes wide, aligned to 4; a vector that
+// would pass the row's end is moved back to end there, and the dot skips what
+// it then shares with the vector before it.
+typedef uint32_t raw4_e4 __attribute__((ext_vector_type(4), aligned(4)));
 
 template <typename T, int VEC, int LPN, int NCH>
+__device__ inline void load_row_ragged(const T* __restrict__ row, int q, int kz,
+                                       float (&x)[NCH][VEC]) {
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    const int w = (q + ch * LPN) * VEC;
+    const raw4_e4 r = *reinterpret_cast<const raw4_e4*>(row + (w < kz - VEC ? w : kz - VEC));
+    Unpack<T, VEC>::run(make_uint4(r.x, r.y, r.z, r.w), x[ch]);
+  }
+}
+
+template <int VEC, int LPN, int NCH>
+__device__ inline float lane_dot_ragged(const float (&a)[NCH][VEC], const float (&b)[NCH][VEC],
+                                        int q, int kz) {
+  float acc = 0.f;
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch) {
+    const int skip = (q + ch * LPN) * VEC - (kz - VEC);   // >= VEC: past the row's end
+#pragma unroll
+    for (int t = 0; t < VEC; ++t) {
+      const float f = fmaf(a[ch][t], b[ch][t], acc);
+      acc = t >= skip ? f : acc;
+    }
+  }
+  return acc;
+}
+
+// ------------------------------------------------------------------ SDDMM
+
+template <typename T, int VEC, int LPN, int NCH, bool RAGGED>
 __global__ __launch_bounds__(256) void k_sddmm(int64_t nnz, int64_t nitems, int64_t nblocks,
                                                int wslots, const int32_t* __restrict__ colidx,
                                                const uint64_t* __restrict__ head,
@@ -154,12 +187,22 @@ __global__ __launch_bounds__(256) void k_sddmm(int64_t nnz, int64_t nitems, int6
         const int src = g * LPN + j0 + jj;
         const int c = __shfl(col, src);
         const int r = __shfl(row, src);
-        load_row<T, VEC, LPN, NCH>(A + (int64_t)r * kz, q, nvec, a[jj]);
-        load_row<T, VEC, LPN, NCH>(B + (int64_t)c * kz, q, nvec, bb[jj]);
+        if constexpr (RAGGED) {
+          load_row_ragged<T, VEC, LPN, NCH>(A + (int64_t)r * kz, q, kz, a[jj]);
+          load_row_ragged<T, VEC, LPN, NCH>(B + (int64_t)c * kz, q, kz, bb[jj]);
+        } else {
+          load_row<T, VEC, LPN, NCH>(A + (int64_t)r * kz, q, nvec, a[jj]);
+          load_row<T, VEC, LPN, NCH>(B + (int64_t)c * kz, q, nvec, bb[jj]);
+        }
       }
 #pragma unroll
       for (int jj = 0; jj < JB; ++jj) {
-        const float d = group_sum<LPN>(lane_dot<VEC, LPN, NCH>(a[jj], bb[jj], q, nvec));
+        float l;
+        if constexpr (RAGGED)
+          l = lane_dot_ragged<VEC, LPN, NCH>(a[jj], bb[jj], q, kz);
+        else
+          l = lane_dot<VEC, LPN, NCH>(a[jj], bb[jj], q, nvec);
+        const float d = group_sum<LPN>(l);
         if (q == j0 + jj) res = d;
       }
     }
@@ -953,12 +996,52 @@ inline spc3d_status pick_shape(int kz, spc3d_dtype t, bool vec_ok, int variant, 
     default: { constexpr int LPN_ = 64; __VA_ARGS__; break; } \
   }
 
+// The ragged shape of an automatic-variant SDDMM on rows that pick_shape reads
+// element by element.  us with one element a lane / 16-byte vectors: R-MAT
+// 2^18, degree 16, kz = 12 44.4 / 38.5, 20 58.1 / 45.9, 30 59.5 / 49.8, 60 84.2
+// / 66.3, 100 159.1 / 103.5, 250 427 / 217; 2^19, degree 32, kz = 60 325 / 273;
+// banded kz = 30 86.5 / 68.6; uniform kz = 60 97.4 / 98.4.  Odd kz, whose rows
+// are 2-byte aligned, loses (17: 57.9 / 69.7, 33: 82.1 / 83.4), and FP32 rows,
+// bound by the two lines each touches, stay as they are (kz = 30 64.4 / 61.9,
+// 50 89.5 / 93.8).
+inline bool pick_ragged(int kz, spc3d_dtype t, const void* A, const void* B, Shape* sh) {
+  if (t != SPC3D_BF16 || sh->vec != 1 || kz < 8 || kz % 2) return false;
+  if ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 3u) return false;
+  const int nvec = (kz + 7) / 8;   // at most 32: pick_shape takes kz up to kMaxKzScalar
+  sh->vec = 8;
+  sh->lanes = nvec <= 2 ? 2 : nvec <= 4 ? 4 : nvec <= 8 ? 8 : 16;
+  sh->nch = (nvec + sh->lanes - 1) / sh->lanes;
+  return true;
+}
+static_assert(kMaxKzScalar <= 2 * 16 * 8, "two vectors a lane cover the widest ragged row");
+
+template <typename T, int VEC>
+void launch_sddmm_ragged(const Shape& sh, hipStream_t st, int64_t nnz, int64_t nitems,
+                         int64_t nblocks, const Orient& o, const float* vals, const void* A,
+                         const void* B, int kz, float* out, int accumulate) {
+#define SPC3D_RAGGED(L, N)                                                                      \
+  hipLaunchKernelGGL((k_sddmm<T, VEC, L, N, true>), dim3((unsigned)nblocks), dim3(256), 0, st,  \
+                     nnz, nitems, nblocks, sh.items, o.idx, o.head, o.tile_row, vals,           \
+                     static_cast<const T*>(A), static_cast<const T*>(B), kz, out, accumulate)
+  if (sh.nch == 2)
+    SPC3D_RAGGED(16, 2);
+  else if (sh.lanes == 2)
+    SPC3D_RAGGED(2, 1);
+  else if (sh.lanes == 4)
+    SPC3D_RAGGED(4, 1);
+  else if (sh.lanes == 8)
+    SPC3D_RAGGED(8, 1);
+  else
+    SPC3D_RAGGED(16, 1);
+#undef SPC3D_RAGGED
+}
+
 template <typename T, int VEC>
 void launch_sddmm(const Shape& sh, hipStream_t st, int64_t nnz, int64_t nitems, int64_t nblocks,
                   const Orient& o, const float* vals, const void* A, const void* B, int kz,
                   float* out, int accumulate) {
   SPC3D_SWITCH_LPN(sh.lanes, SPC3D_SWITCH_NCH(sh.nch,
-      hipLaunchKernelGGL((k_sddmm<T, VEC, LPN_, NCH_>), dim3((unsigned)nblocks), dim3(256), 0,
+      hipLaunchKernelGGL((k_sddmm<T, VEC, LPN_, NCH_, false>), dim3((unsigned)nblocks), dim3(256), 0,
                          st, nnz, nitems, nblocks, sh.items, o.idx, o.head, o.tile_row, vals,
                          static_cast<const T*>(A), static_cast<const T*>(B), kz, out,
                          accumulate)));
