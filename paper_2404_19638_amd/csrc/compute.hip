@@ -38,16 +38,17 @@ namespace {
 // columns do not gain: 2^20 columns, 32 entries each, kz = 64 1248 / - / 1344.
 // So only blocks whose entries use fewer columns than uniform positions would
 // (0.8 of the expected number) are sliced.  The fused pass reads A and adds to
-// the dots once more per slice, so it slices only rows of 384 bytes or more of
+// the dots once more per slice, so it slices only rows of 512 bytes or more of
 // tables beyond 128 MB: R-MAT 2^20 kz = 128 1867 / 1662 / 1712, 2^19 833 /
-// 767 / 874, 2^18 372 / 368 / 451, kz = 64 2^20 820 / - / 829.
+// 767 / 874, 2^18 372 / 368 / 451, kz = 64 2^20 820 / - / 829; at kz = 96, three
+// slices of 128 bytes, 2^20 vertices of degree 8 took 449 against 401.
 int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
   const int64_t rows = transpose ? p->R : p->C;   // of the gathered table
   const double ids = transpose ? (double)(p->row_hi - p->row_lo) : (double)(p->col_hi - p->col_lo);
   if (row_bytes % 128 || rows >= 0.8 * ids * -expm1(-(double)p->nnz / ids)) return 1;
   const int64_t lines = row_bytes / 128, table = rows * row_bytes;
   constexpr int64_t MB = 1 << 20;
-  if (lines < (fused ? 3 : 2)) return 1;
+  if (lines < (fused ? 4 : 2)) return 1;
   if (table <= (fused ? 128 : lines == 2 ? 64 : 40) * MB) return 1;
   if (lines % 2 == 0 && lines >= 4 && (fused || table / (lines / 2) <= 64 * MB))
     return (int)(lines / 2);
@@ -70,13 +71,30 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // shorter run is faster: R-MAT 2^16, kz = 32 at 16 / 32 / 64 slots 34.6 / 28.2 /
 // 33.6, 2^15 20.8 / 21.9 / 24.8.
 //
+// With two or more vectors a lane the SpMM takes 64 from 4000 wavefronts on
+// (R-MAT 2^18, degree 12, kz = 96 101 / 98; uniform, 3M entries, kz = 128 218 /
+// 214) and 32 from 6000 (uniform, 1.6M, kz = 96 84.0 at 16 / 81.6), and the fused
+// pass 64 from 4000 at four vectors (uniform, 3M, kz = 128 232 / 225).
+//
+// Left to the shapes of pick_shape from 2^17 entries on, where those read whole
+// vectors (vec_ok: the operands' alignment; us there / here): four vectors a lane on
+// short rows, whose row ends cost more than the steps between them (SpMM
+// below 10 entries a row: banded, 7, kz = 96 32.6 / 33.8, uniform, 4, 62.8 /
+// 64.6; fused below 20: uniform, 4, kz = 96 75.6 / 82.1, banded, 12, 40,000
+// rows, kz = 128 28.2 / 30.7); bfloat16 rows of 256 bytes, fused, below 5 entries
+// (uniform, 4, 67.3 / 71.6); and in the SpMM from 2^21 entries on, where
+// pick_shape's items of 512 slots begin (R-MAT 2^18, degree 12, 76.0 / 79.7; 2^17,
+// degree 24, 66.2 / 70.8; banded kz = 96 197 / 230, though 2^18, degree 32, 165 /
+// 157).
+//
 // Rows of A.  With one vector a lane, loading the slot's row of A for every
 // slot (from L1 mostly) costs less than loading it under a mask where a row
 // starts, unless rows are long: 79.6 against 84.2 us on the 2^24-vertex share
 // (9.5 entries a row), 100.7 against 95.6 on R-MAT 2^18 (44), kz = 32.  With
 // more vectors a lane the L1 traffic decides: banded, 12 entries, kz = 128 892
 // against 682 us.
-bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, RunShape* sh) {
+bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, bool vec_ok,
+              RunShape* sh) {
   const int esz = t == SPC3D_F32 ? 4 : 2;
   sh->vec = 16 / esz;
   const int64_t most = p->R > p->C ? p->R : p->C;
@@ -90,10 +108,18 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, R
   sh->full = sh->kw == sh->lanes * sh->nch * sh->vec;
   const int64_t rows = transpose ? p->C : p->R;
   const bool len16 = p->nnz >= 16 * rows;
+  if (vec_ok && kz % sh->vec == 0 && p->nnz >= (int64_t(1) << 17)) {
+    const bool wide_bf16 = t == SPC3D_BF16 && sh->nch == 2;
+    if (sh->nch == 4 && p->nnz < (fused ? 20 : 10) * rows) return false;
+    if (wide_bf16 && fused && p->nnz < 5 * rows) return false;
+    if (wide_bf16 && !fused && sh->slices == 1 && p->nnz >= (int64_t(1) << 21)) return false;
+  }
   sh->each_row = len16;
   const int64_t G = 64 / sh->lanes;
   const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);
-  sh->lg_s = long_runs && p->nnz >= 7000 * 64 * G ? 6 : p->nnz >= 7000 * 32 * G ? 5 : 4;
+  const int64_t from64 = (fused ? sh->nch == 4 : sh->nch >= 2) ? 4000 : 7000;
+  const int64_t from32 = !fused && sh->nch >= 2 ? 6000 : 7000;
+  sh->lg_s = long_runs && p->nnz >= from64 * 64 * G ? 6 : p->nnz >= from32 * 32 * G ? 5 : 4;
   return true;
 }
 
@@ -153,7 +179,7 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
   spc3d_status st = pick_shape(kz, x_t, al, variant, fused ? 2 : 1, p->nnz, &sh);
   if (st != SPC3D_OK) return st;
   RunShape rs;
-  const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, &rs) &&
+  const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, al, &rs) &&
                    buf_bytes >= (size_t)carry_bytes(p->nnz, rs.item(), kz);
   const int64_t nitems = (p->nnz + sh.items - 1) / sh.items;
   const size_t need = (size_t)nitems * 2 * (size_t)kz * 4;
@@ -327,7 +353,7 @@ spc3d_status spc3d_spmm_buffer_size(spc3d_plan h, int transpose, int32_t kz, int
     for (int f = 0; f < 2; ++f)
       for (int t = 0; t < 2; ++t) {
         RunShape rs;
-        if (!pick_run(p, transpose, f != 0, kz, t ? SPC3D_BF16 : SPC3D_F32, &rs)) continue;
+        if (!pick_run(p, transpose, f != 0, kz, t ? SPC3D_BF16 : SPC3D_F32, false, &rs)) continue;
         const size_t n = (size_t)carry_bytes(p->nnz, rs.item(), kz);
         if (n > *bytes) *bytes = n;
       }
