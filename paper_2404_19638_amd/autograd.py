@@ -33,13 +33,21 @@ def _needs(ctx, i):
     return ctx.needs_input_grad[i]
 
 
+# Stored entries up to which the transposed SpMM reads its values through the
+# slot map.  us through the map / permuted first (permute + SpMM; MI355X, R-MAT
+# of degree 32, FP32): 1.8M entries kz = 32 31.7 / 37.8, kz = 64 42.6 / 48.6; 7.6M
+# 129 / 144, 205 / 206; 31.4M 755 / 669, 1530 / 989 (the 126 MB of values miss L2,
+# once per slice).  At 53,000 entries 9.2 / 13.7: a launch less.
+DIRECT_MAX_NNZ = 1 << 22
+
+
 def _spmm_t(plan, vals, X):
-    """Transposed SpMM (sum over each column's entries).  Values are first
-    permuted to column-major order so the kernel reads them as one stream
-    rather than one random load per entry through the slot map (the same
-    results, bit for bit)."""
-    if vals is None:
-        return spc.spmm(plan, None, X, transpose=1)
+    """Transposed SpMM (sum over each column's entries).  On large blocks the
+    values are first permuted to column-major order so the kernel reads them as
+    one stream rather than one random load per entry through the slot map (the
+    same results, bit for bit)."""
+    if vals is None or plan.nnz <= DIRECT_MAX_NNZ:
+        return spc.spmm(plan, vals, X, transpose=1)
     vt = spc.permute_values(plan, spc.SLOT_TO_COLUMN, vals)
     return spc.spmm(plan, vt, X, transpose=2)
 
