@@ -347,6 +347,16 @@ spc3d_status spc3d_row_softmax_bwd(spc3d_plan plan, const float* d_alpha, const 
                                    float* d_de, void* d_buf, size_t buf_bytes,
                                    hipStream_t stream);
 
+/* spc3d_row_softmax_bwd, and alpha and de in the column-major order of a plan
+ * built with SPC3D_BUILD_CSC as well (as SLOT_TO_COLUMN permutes them) in d_alpha_t
+ * and d_de_t, for the transposed products that follow.  d_pairs is scratch of
+ * 2 * nnz FP32 values, 8-byte aligned; d_alpha_t, d_de_t and d_pairs alias
+ * nothing else. */
+spc3d_status spc3d_row_softmax_bwd_columns(spc3d_plan plan, const float* d_alpha,
+                                           const float* d_dalpha, float* d_de, float* d_alpha_t,
+                                           float* d_de_t, float* d_pairs, void* d_buf,
+                                           size_t buf_bytes, hipStream_t stream);
+
 /* alpha[p] = exp(e[p] - stats[2r]) / stats[2r+1] for every entry p of local
  * row r: the softmax weights rebuilt from scores and the per-row (max, sum of
  * exp(e - max)) that spc3d_attention_fwd stores.  d_stats holds 2R floats

@@ -170,6 +170,48 @@ class ScatterReduceFn(torch.autograd.Function):
         return None, None, dpacked, dout, None
 
 
+def _attention_bwd(needs, plan, alpha, dout, Q, Kf, V):
+    """(dQ, dKf, dV) of out = alpha . V, alpha = rowsoftmax(SDDMM(Q, Kf)); None
+    where not needed.  On blocks beyond DIRECT_MAX_NNZ whose two transposed
+    products both follow, one pass takes alpha and de to column order."""
+    dout = dout.to(V.dtype)   # the upstream gradient in the operands' type
+    dQ = dK = dV = de = at = det = None
+    if needs[0] or needs[1]:
+        dalpha = spc.sddmm(plan, None, dout, V)
+        if needs[1] and needs[2] and plan.nnz > DIRECT_MAX_NNZ:
+            de, at, det = spc.row_softmax_bwd_columns(plan, alpha, dalpha, out=dalpha)
+        else:
+            de = spc.row_softmax_bwd(plan, alpha, dalpha, out=dalpha)
+    if needs[0]:
+        dQ = _as(spc.spmm(plan, de, Kf, transpose=0), Q)
+    if needs[1]:
+        dK = _as(_spmm_t(plan, de, Q) if det is None
+                 else spc.spmm(plan, det, Q, transpose=2), Kf)
+    if needs[2]:
+        dV = _as(_spmm_t(plan, alpha, dout) if at is None
+                 else spc.spmm(plan, at, dout, transpose=2), V)
+    return dQ, dK, dV
+
+
+class AttentionFn(torch.autograd.Function):
+    """out = rowsoftmax(SDDMM(pattern, Q, Kf)) . V in the three kernels, with
+    alpha kept for the backward."""
+
+    @staticmethod
+    def forward(ctx, plan, Q, Kf, V):
+        Q, Kf, V = Q.contiguous(), Kf.contiguous(), V.contiguous()
+        alpha = spc.row_softmax(plan, spc.sddmm(plan, None, Q, Kf))
+        ctx.plan = plan
+        ctx.save_for_backward(Q, Kf, V, alpha)
+        return spc.spmm(plan, alpha, V)
+
+    @staticmethod
+    def backward(ctx, dout):
+        Q, Kf, V, alpha = ctx.saved_tensors
+        return None, *_attention_bwd(ctx.needs_input_grad[1:], ctx.plan, alpha,
+                                     dout.contiguous(), Q, Kf, V)
+
+
 class FusedAttentionFn(torch.autograd.Function):
     """out = rowsoftmax(SDDMM(pattern, Q, Kf)) . V in one fused pass
     (spc3d_attention_fwd).  The backward recomputes the scores with one SDDMM,
@@ -189,20 +231,10 @@ class FusedAttentionFn(torch.autograd.Function):
     def backward(ctx, dout):
         plan = ctx.plan
         Q, Kf, V, stats = ctx.saved_tensors
-        dout = dout.contiguous()
         e = spc.sddmm(plan, None, Q, Kf)
         alpha = spc.row_softmax_apply(plan, e, stats, out=e)
-        dout = dout.to(V.dtype)   # the upstream gradient in the operands' type
-        dalpha = spc.sddmm(plan, None, dout, V)
-        de = spc.row_softmax_bwd(plan, alpha, dalpha, out=dalpha)
-        dQ = dK = dV = None
-        if _needs(ctx, 1):
-            dQ = _as(spc.spmm(plan, de, Kf, transpose=0), Q)
-        if _needs(ctx, 2):
-            dK = _as(_spmm_t(plan, de, Q), Kf)
-        if _needs(ctx, 3):
-            dV = _as(_spmm_t(plan, alpha, dout), V)
-        return None, dQ, dK, dV
+        return None, *_attention_bwd(ctx.needs_input_grad[1:], plan, alpha, dout.contiguous(),
+                                     Q, Kf, V)
 
 
 def sddmm(plan, vals, A, B):
@@ -277,6 +309,4 @@ def gnn_attention(plan, Q, Kf, V, fused: bool | None = None):
     if fused:
         _need_fused(Q, Kf, V)
         return FusedAttentionFn.apply(plan, Q, Kf, V)
-    e = sddmm(plan, None, Q, Kf)
-    alpha = row_softmax(plan, e)
-    return spmm(plan, alpha, V, 0)
+    return AttentionFn.apply(plan, Q, Kf, V)

@@ -210,12 +210,12 @@ __global__ __launch_bounds__(256) void k_row_reduce_fixup(int64_t nnz, int64_t n
 // then row stats).  Eight windows measured 2-3% faster than four.
 constexpr int kApplyWin = 8;
 
-template <class Op>
+template <class Op, bool PAIRS = false>
 __device__ inline void apply_windows(int64_t nnz, const uint64_t* __restrict__ head,
                                      const int32_t* __restrict__ tile_row,
                                      const typename Op::St* __restrict__ stats,
                                      const float* __restrict__ x0, const float* __restrict__ x1,
-                                     float* __restrict__ y) {
+                                     float* __restrict__ y, float2* __restrict__ pairs = nullptr) {
   const int lane = threadIdx.x & 63;
   const int64_t nwin = (nnz + 63) >> 6;
   const int64_t ngrp = (nwin + kApplyWin - 1) / kApplyWin;
@@ -237,7 +237,11 @@ __device__ inline void apply_windows(int64_t nnz, const uint64_t* __restrict__ h
     for (int k = 0; k < kApplyWin; ++k) {
       const int64_t p = (gi * kApplyWin + k) * 64 + lane;
       const typename Op::St st = stats[row[k]];
-      if (p < nnz) y[p] = Op::apply(a[k], da[k], st);
+      const float o = Op::apply(a[k], da[k], st);
+      if (p < nnz) {
+        y[p] = o;
+        if constexpr (PAIRS) pairs[p] = make_float2(a[k], o);
+      }
     }
   }
 }
@@ -269,6 +273,31 @@ __global__ __launch_bounds__(256) void k_softmax_bwd_apply(int64_t nnz,
                                                            const float* __restrict__ dalpha,
                                                            float* __restrict__ de) {
   apply_windows<SoftmaxBwdApply>(nnz, head, tile_row, stats, alpha, dalpha, de);
+}
+
+// The backward that also leaves (alpha, de) side by side, and the pass that
+// takes both to column order.  A permutation reads one 4-byte value per entry
+// from a line of its own, and lines are what bound it (343 us for 31.4M entries,
+// whose two streams take 40): two values from one line cost what one does.  us
+// for a whole training step, two permutations / this (MI355X, K = 64): R-MAT
+// 2^20, degree 32, FP32 5002 / 4773, bfloat16 3296 / 3088; 2^18, degree 28, FP32
+// 955 / 930; uniform, 6.5M entries, 1765 / 1691.
+__global__ __launch_bounds__(256) void k_softmax_bwd_apply_pairs(
+    int64_t nnz, const uint64_t* __restrict__ head, const int32_t* __restrict__ tile_row,
+    const DotSum::St* __restrict__ stats, const float* __restrict__ alpha,
+    const float* __restrict__ dalpha, float* __restrict__ de, float2* __restrict__ pairs) {
+  apply_windows<SoftmaxBwdApply, true>(nnz, head, tile_row, stats, alpha, dalpha, de, pairs);
+}
+
+__global__ void k_permute_pairs(int64_t nnz, const int32_t* __restrict__ slot,
+                                const float2* __restrict__ pairs, float* __restrict__ a,
+                                float* __restrict__ b) {
+  for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < nnz;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const float2 v = pairs[slot[t]];
+    a[t] = v.x;
+    b[t] = v.y;
+  }
 }
 
 __global__ void k_mul_values(int64_t n, const float* __restrict__ a, const float* __restrict__ b,
@@ -327,6 +356,36 @@ spc3d_status row_reduce(const Plan* p, const float* x0, const float* x1, void* b
   return SPC3D_OK;
 }
 
+// pairs: where (alpha, de) go side by side, or nullptr.
+spc3d_status softmax_bwd(spc3d_plan h, const float* d_alpha, const float* d_dalpha, float* d_de,
+                         void* d_buf, size_t buf_bytes, hipStream_t stream, float2* pairs) {
+  Plan* p;
+  spc3d_status st = get_plan(h, &p);
+  if (st != SPC3D_OK) return st;
+  if (p->nnz == 0) return SPC3D_OK;
+  if (!d_alpha || !d_dalpha || !d_de || !d_buf)
+    return fail(SPC3D_ERR_INVALID_ARG, "NULL buffer");
+  if (reinterpret_cast<uintptr_t>(d_buf) & 255u)
+    return fail(SPC3D_ERR_INVALID_ARG, "buffer must be 256-byte aligned");
+  if (buf_bytes < softmax_buffer_bytes(p))
+    return fail(SPC3D_ERR_WORKSPACE, "softmax buffer too small");
+  DeviceGuard dg;
+  st = dg.enter(p);
+  if (st != SPC3D_OK) return st;
+  SPC3D_DEBUG_CHECK(p, stream);
+  DotSum::St* stats;
+  st = row_reduce<DotSum>(p, d_alpha, d_dalpha, d_buf, stream, &stats);
+  if (st != SPC3D_OK) return st;
+  if (pairs)
+    hipLaunchKernelGGL(k_softmax_bwd_apply_pairs, dim3(apply_blocks(p->nnz)), dim3(256), 0, stream,
+                       p->nnz, p->head, p->tile_row, stats, d_alpha, d_dalpha, d_de, pairs);
+  else
+    hipLaunchKernelGGL(k_softmax_bwd_apply, dim3(apply_blocks(p->nnz)), dim3(256), 0, stream,
+                       p->nnz, p->head, p->tile_row, stats, d_alpha, d_dalpha, d_de);
+  SPC3D_LAUNCHED("softmax bwd apply");
+  return SPC3D_OK;
+}
+
 }  // namespace
 }  // namespace spc3d
 
@@ -370,26 +429,31 @@ spc3d_status spc3d_row_softmax(spc3d_plan h, const float* d_e, float* d_alpha, v
 spc3d_status spc3d_row_softmax_bwd(spc3d_plan h, const float* d_alpha, const float* d_dalpha,
                                    float* d_de, void* d_buf, size_t buf_bytes,
                                    hipStream_t stream) {
+  return softmax_bwd(h, d_alpha, d_dalpha, d_de, d_buf, buf_bytes, stream, nullptr);
+}
+
+spc3d_status spc3d_row_softmax_bwd_columns(spc3d_plan h, const float* d_alpha,
+                                           const float* d_dalpha, float* d_de, float* d_alpha_t,
+                                           float* d_de_t, float* d_pairs, void* d_buf,
+                                           size_t buf_bytes, hipStream_t stream) {
   Plan* p;
   spc3d_status st = get_plan(h, &p);
   if (st != SPC3D_OK) return st;
+  if (!(p->flags & SPC3D_BUILD_CSC))
+    return fail(SPC3D_ERR_INVALID_ARG, "column-major order needs a plan built with BUILD_CSC");
   if (p->nnz == 0) return SPC3D_OK;
-  if (!d_alpha || !d_dalpha || !d_de || !d_buf)
-    return fail(SPC3D_ERR_INVALID_ARG, "NULL buffer");
-  if (reinterpret_cast<uintptr_t>(d_buf) & 255u)
-    return fail(SPC3D_ERR_INVALID_ARG, "buffer must be 256-byte aligned");
-  if (buf_bytes < softmax_buffer_bytes(p))
-    return fail(SPC3D_ERR_WORKSPACE, "softmax buffer too small");
+  if (!d_alpha_t || !d_de_t || !d_pairs) return fail(SPC3D_ERR_INVALID_ARG, "NULL buffer");
+  if (reinterpret_cast<uintptr_t>(d_pairs) & 7u)
+    return fail(SPC3D_ERR_INVALID_ARG, "pairs must be 8-byte aligned");
+  float2* pairs = reinterpret_cast<float2*>(d_pairs);
+  st = softmax_bwd(h, d_alpha, d_dalpha, d_de, d_buf, buf_bytes, stream, pairs);
+  if (st != SPC3D_OK) return st;
   DeviceGuard dg;
   st = dg.enter(p);
   if (st != SPC3D_OK) return st;
-  SPC3D_DEBUG_CHECK(p, stream);
-  DotSum::St* stats;
-  st = row_reduce<DotSum>(p, d_alpha, d_dalpha, d_buf, stream, &stats);
-  if (st != SPC3D_OK) return st;
-  hipLaunchKernelGGL(k_softmax_bwd_apply, dim3(apply_blocks(p->nnz)), dim3(256), 0, stream,
-                     p->nnz, p->head, p->tile_row, stats, d_alpha, d_dalpha, d_de);
-  SPC3D_LAUNCHED("softmax bwd apply");
+  hipLaunchKernelGGL(k_permute_pairs, dim3(blocks_for(p->nnz)), dim3(256), 0, stream, p->nnz,
+                     p->slot_t, pairs, d_alpha_t, d_de_t);
+  SPC3D_LAUNCHED("permute pairs");
   return SPC3D_OK;
 }
 

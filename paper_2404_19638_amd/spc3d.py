@@ -85,6 +85,7 @@ def lib():
         "spc3d_row_softmax": [vp, vp, vp, vp, sz, vp],
         "spc3d_row_softmax_bwd": [vp, vp, vp, vp, vp, sz, vp],
         "spc3d_mul_values": [vp, vp, vp, vp, vp],
+        "spc3d_row_softmax_bwd_columns": [vp, vp, vp, vp, vp, vp, vp, vp, sz, vp],
         "spc3d_row_softmax_apply": [vp, vp, vp, vp, vp],
         "spc3d_lambda_owners_workspace_size": [i64, i64, P(sz)],
         "spc3d_lambda_owners": [i32, vp, vp, i64, i64, vp, vp, vp, vp, vp, vp, sz, vp],
@@ -526,6 +527,26 @@ def row_softmax_bwd(plan: Plan, alpha: torch.Tensor, dalpha: torch.Tensor, out=N
                                        _ptr(buf), buf.numel(), _stream(stream)),
            "spc3d_row_softmax_bwd")
     return out
+
+
+def row_softmax_bwd_columns(plan: Plan, alpha: torch.Tensor, dalpha: torch.Tensor, out=None):
+    """row_softmax_bwd, with alpha and the result in column-major order too (a
+    plan with BUILD_CSC): returns (de, alpha_t, de_t).  Runs on the current
+    stream, which the scratch it allocates and drops belongs to."""
+    for t in (alpha, dalpha):
+        _need(t.dtype == torch.float32 and t.is_contiguous() and t.numel() >= plan.nnz,
+              "alpha and dalpha must hold nnz FP32 values")
+    out = torch.empty_like(alpha) if out is None else out
+    _need(out.dtype == torch.float32 and out.is_contiguous() and out.numel() >= plan.nnz,
+          "out must hold nnz FP32 values")
+    alpha_t, de_t = torch.empty_like(alpha), torch.empty_like(alpha)
+    pairs = torch.empty(2 * plan.nnz, dtype=torch.float32, device=alpha.device)
+    buf = plan.buffer("softmax", plan.size("softmax", lambda: row_softmax_buffer_size(plan)))
+    _check(lib().spc3d_row_softmax_bwd_columns(plan.handle, _ptr(alpha), _ptr(dalpha), _ptr(out),
+                                               _ptr(alpha_t), _ptr(de_t), _ptr(pairs), _ptr(buf),
+                                               buf.numel(), _stream()),
+           "spc3d_row_softmax_bwd_columns")
+    return out, alpha_t, de_t
 
 
 def row_softmax_apply(plan: Plan, e: torch.Tensor, stats: torch.Tensor, out=None, stream=None):
