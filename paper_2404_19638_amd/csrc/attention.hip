@@ -549,6 +549,10 @@ spc3d_status spc3d_attention_fwd(spc3d_plan h, const void* d_Q, const void* d_K,
     return fail(SPC3D_ERR_INVALID_ARG, "stats must be 8-byte aligned");
   if (reinterpret_cast<uintptr_t>(d_buf) & 255u)
     return fail(SPC3D_ERR_INVALID_ARG, "buffer must be 256-byte aligned");
+  // shorter runs mean more carries: a buffer for fewer takes longer runs
+  while (variant < 0 && sh.lg_s < 6 &&
+         buf_bytes < (size_t)attn_items(p, sh) * 2 * (size_t)(kz + 4) * 4)
+    ++sh.lg_s;
   const int64_t nitems = attn_items(p, sh);
   const size_t need = (size_t)nitems * 2 * (size_t)(kz + 4) * 4;
   if (buf_bytes < need)

@@ -57,3 +57,26 @@ def test_items_that_end_anywhere(dtype, kz, lg_lanes, lg_s):
         ref = oracle.relabel(rows, cols, (0, R), (0, nnz))
         fused._check(spc, plan, ref, Q, K, V, kz, dtype, lg_lanes | lg_s << 4,
                      f"{dtype} kz={kz} nnz={nnz}", rounded)
+
+
+@pytest.mark.parametrize("lg_s", [4, 5, 6])
+def test_a_smaller_buffer_takes_longer_runs(lg_s):
+    """The automatic shape with a buffer of an explicit run length's size gives
+    that run length's result; one byte less than the longest's is refused."""
+    from paper_2404_19638_amd import spc3d as spc
+    n, kz = 3000, 64
+    key = torch.arange(0, n * n, 601, device=DEV)
+    plan = spc.plan_create_coo(key // n, key % n, (0, n), (0, n))
+    g = torch.Generator(device=DEV).manual_seed(5)
+    Q, K, V = (torch.rand((r, kz), device=DEV, generator=g) for r in (plan.R, plan.C, plan.C))
+    v = 4 | lg_s << 4
+    size = spc.attention_fwd_buffer_size(plan, kz, spc.F32, v)
+    buf = torch.empty(size, dtype=torch.uint8, device=DEV)
+    print(f"attention: nnz={plan.nnz} buffer={size}", file=sys.stderr, flush=True)
+    want, _ = spc.attention_fwd(plan, Q, K, V, variant=v)
+    got, _ = spc.attention_fwd(plan, Q, K, V, buf=buf)
+    assert torch.equal(got, want)
+    if lg_s == 6:
+        with pytest.raises(spc.Spc3dError) as e:
+            spc.attention_fwd(plan, Q, K, V, buf=buf[:size - 1])
+        assert e.value.status == spc.ERR_WORKSPACE
