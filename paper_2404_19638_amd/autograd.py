@@ -265,19 +265,25 @@ def _need_fused(Q, Kf, V):
         raise ValueError("the fused attention pass needs 16-byte aligned Q, Kf and V")
 
 
-# Largest FP32 block (stored entries) on which the automatic choice takes the
-# one-pass forward: it measured faster at 1.8M entries (R-MAT 2^16, K = 64) and
-# slower from 7.6M entries (2^18) on, where the Kf and V rows it keeps live
-# together outgrow the Infinity Cache.  With bfloat16 operands it measured
-# faster at every size up to 31.4M entries (2^20).
+# Largest block (stored entries) on which the automatic choice takes the
+# one-pass forward, by the bytes of a row of Kf: its two rows a slot are live
+# together, so wide rows outgrow the caches earlier than the three kernels, which
+# also take wide rows of skewed columns in slices.  us three kernels / one pass
+# (MI355X, R-MAT): 128-byte rows gain at every size (FP32 K = 32, 1.8M entries
+# 64.9 / 45.1, 31.4M 782 / 773; bfloat16 K = 64 871 / 811).  256 bytes: FP32 2.8M
+# 128 / 120, 3.0M 144 / 147, 7.6M 314 / 336; bfloat16 K = 128 7.6M 369 / 357, 15.5M
+# 763 / 825.  512 bytes: FP32 K = 128 883,000 82.4 / 77.3, 955,000 92.6 / 97.8, 1.8M
+# 147 / 162; bfloat16 K = 256 955,000 111 / 108, 7.6M 663 / 871.
 AUTO_FUSED_F32_MAX_NNZ = 1 << 21
+_AUTO_FUSED_MAX_NNZ = {(spc.F32, 256): AUTO_FUSED_F32_MAX_NNZ, (spc.F32, 512): 900_000,
+                       (spc.BF16, 256): 1 << 23, (spc.BF16, 512): 1 << 20}
 
 
 def _auto_fused(plan, Q, Kf, V):
     """The forward gnn_attention takes when the caller leaves it open: the
     one-pass kernel for inference (no gradient is recorded) where it measured
     faster, the three kernels otherwise (the fused backward recomputes the
-    scores, and the fused forward loses in FP32 on large blocks)."""
+    scores, and the fused forward loses with wide rows on large blocks)."""
     if torch.is_grad_enabled() and any(t.requires_grad for t in (Q, Kf, V)):
         return False
     if not (Q.dtype == Kf.dtype == V.dtype) or Q.dtype not in (torch.float32, torch.bfloat16):
@@ -287,7 +293,8 @@ def _auto_fused(plan, Q, Kf, V):
         return False
     if not all(t.is_contiguous() and t.data_ptr() % 16 == 0 for t in (Q, Kf, V)):
         return False
-    return dt == spc.BF16 or plan.nnz <= AUTO_FUSED_F32_MAX_NNZ
+    limit = _AUTO_FUSED_MAX_NNZ.get((dt, Q.shape[1] * Q.element_size()))
+    return limit is None or plan.nnz <= limit
 
 
 def gnn_attention(plan, Q, Kf, V, fused: bool | None = None):
@@ -298,11 +305,9 @@ def gnn_attention(plan, Q, Kf, V, fused: bool | None = None):
     fused=True runs the forward as one pass (spc3d_attention_fwd; K must be
     covered by it, see spc.attention_supported) and recomputes the scores in
     the backward; fused=False runs the three separate kernels.  Left as None,
-    the one-pass forward is taken for inference (no gradient recorded) with
-    bfloat16 operands, or FP32 operands on blocks of up to
-    AUTO_FUSED_F32_MAX_NNZ entries, and the three kernels otherwise: the
-    layer is bound by the gathers of Kf and V rows, which the fused pass
-    keeps live together, so in FP32 it measured slower on large blocks.
+    the one-pass forward is taken for inference (no gradient recorded) where it
+    measured faster: rows of up to 128 bytes on every block, wider ones up to a
+    number of entries (see _AUTO_FUSED_MAX_NNZ), and the three kernels otherwise.
     """
     if fused is None:
         fused = _auto_fused(plan, Q, Kf, V)
