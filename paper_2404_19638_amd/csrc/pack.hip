@@ -31,8 +31,11 @@ constexpr int kBatch = 2;
 // against 36.5 after 400 MB of other writes.  Nontemporal stores of what the
 // next kernels read again pay only once it outgrows the caches: packed rows
 // beyond 128 MB (uniform share, 229 MB an operand, whole step 418 to 409 us;
-// R-MAT share, 55 MB, 167 to 169), slab rows beyond 32 MB (R-MAT share 52 MB
-// 177 to 167; 2^18 rows kz = 30, 18 MB, 166.5 to 169).  Before, one 16-byte
+// R-MAT share, 55 MB, 167 to 169) and slab rows as far (banded bfloat16, 537 MB,
+// 823 to 784).  Slab rows that a scatter adds to are read nontemporal beyond
+// 32 MB (R-MAT share 55 MB 176 to 165; 2^18 rows kz = 30, 18 MB, 166.5 to 169);
+// stored nontemporal at that size too, the next scatter's reads miss: 36.4
+// against 31.8 us where the same slab is added to again.  Before, one 16-byte
 // chunk a thread at cached accesses, or one element a thread where the width or
 // an address was not a multiple of 16 bytes (whole step, before and after: R-MAT
 // share 173 to 167, uniform 416 to 409, banded bfloat16 820 to 781, kz = 30 182
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(256) void k_gather(int64_t n, int rpw, int c, uint3
 }
 
 // dst[(gmap[l]-lo)*ld + k0 + k] += packed[l*kz + k].
-template <bool NT>
+template <bool NTLD, bool NTST>
 __global__ __launch_bounds__(256) void k_scatter_add(int64_t n, int rpw, int c, uint32_t magic,
                                                      const int64_t* __restrict__ gmap, int64_t lo,
                                                      const float* __restrict__ packed, int kz,
@@ -141,14 +144,14 @@ __global__ __launch_bounds__(256) void k_scatter_add(int64_t n, int rpw, int c, 
       const vec4f_e4* p = reinterpret_cast<const vec4f_e4*>(in + ch.l * kz + ch.e);
       const vec4f_e4* d = reinterpret_cast<const vec4f_e4*>(at[i]);
       v[i] = __builtin_nontemporal_load(p);   // read for the last time
-      w[i] = NT ? __builtin_nontemporal_load(d) : *d;
+      w[i] = NTLD ? __builtin_nontemporal_load(d) : *d;
     }
 #pragma unroll
     for (int i = 0; i < kBatch; ++i) {
       const vec4f_e4 s = w[i] + v[i];
       vec4f_e4* d = reinterpret_cast<vec4f_e4*>(at[i]);
       if (skip[i] == 0) {
-        if constexpr (NT)
+        if constexpr (NTST)
           __builtin_nontemporal_store(s, d);
         else
           *d = s;
@@ -303,11 +306,15 @@ spc3d_status spc3d_scatter_reduce(spc3d_plan h, spc3d_axis axis, const float* d_
                        gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
   } else {
     const RowSplit sp(n, kz, 4);
-    if (n * kz * 4 > kStreamSlab)
-      hipLaunchKernelGGL(k_scatter_add<true>, sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
+    const int64_t bytes = n * kz * 4;
+    if (bytes > kStreamPacked)
+      hipLaunchKernelGGL((k_scatter_add<true, true>), sp.grid, dim3(256), 0, stream, n, sp.rpw,
+                         sp.c, sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
+    else if (bytes > kStreamSlab)
+      hipLaunchKernelGGL((k_scatter_add<true, false>), sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
                          sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
     else
-      hipLaunchKernelGGL(k_scatter_add<false>, sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
+      hipLaunchKernelGGL((k_scatter_add<false, false>), sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
                          sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
   }
   SPC3D_LAUNCHED("scatter_reduce");
