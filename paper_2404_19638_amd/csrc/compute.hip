@@ -41,7 +41,9 @@ namespace {
 // the dots once more per slice, so it slices only rows of 512 bytes or more of
 // tables beyond 128 MB: R-MAT 2^20 kz = 128 1867 / 1662 / 1712, 2^19 833 /
 // 767 / 874, 2^18 372 / 368 / 451, kz = 64 2^20 820 / - / 829; at kz = 96, three
-// slices of 128 bytes, 2^20 vertices of degree 8 took 449 against 401.
+// slices of 128 bytes, 2^20 vertices of degree 8 took 449 against 401.  Nor does it
+// slice rows below 20 entries: the 2^24-vertex share (9.3), kz = 128, 318 whole /
+// 340, the step with the scatter folded in 531 / 606.
 int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
   const int64_t rows = transpose ? p->R : p->C;   // of the gathered table
   const double ids = transpose ? (double)(p->row_hi - p->row_lo) : (double)(p->col_hi - p->col_lo);
@@ -99,14 +101,15 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   sh->vec = 16 / esz;
   const int64_t most = p->R > p->C ? p->R : p->C;
   if (kz < sh->vec || most >= (1 << 24) || most * kz * esz >= (int64_t(1) << 32)) return false;
-  sh->slices = slice_count(p, transpose, fused, (int64_t)kz * esz);
+  const int64_t rows = transpose ? p->C : p->R;
+  // a slice of a fused pass ends every row again, and reads its row of A
+  sh->slices = fused && p->nnz < 20 * rows ? 1 : slice_count(p, transpose, fused, (int64_t)kz * esz);
   sh->kw = kz / sh->slices;
   const int nvec = (sh->kw + sh->vec - 1) / sh->vec;
   if (nvec < 3 || nvec > 32) return false;
   sh->lanes = nvec <= 4 ? 4 : 8;
   sh->nch = nvec <= 8 ? 1 : nvec <= 16 ? 2 : 4;
   sh->full = sh->kw == sh->lanes * sh->nch * sh->vec;
-  const int64_t rows = transpose ? p->C : p->R;
   const bool len16 = p->nnz >= 16 * rows;
   if (vec_ok && kz % sh->vec == 0 && p->nnz >= (int64_t(1) << 17)) {
     const bool wide_bf16 = t == SPC3D_BF16 && sh->nch == 2;
