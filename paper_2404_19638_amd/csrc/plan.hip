@@ -118,6 +118,7 @@ struct Axis {
   int32_t* partial;      // ids of each tile of kWordTile ids
   int32_t* lmap;
   int64_t* gmap;
+  int64_t cap;           // ids gmap has room for, min(nnz, range)
   int32_t* count;        // ids in use
 };
 
@@ -218,7 +219,9 @@ __global__ __launch_bounds__(1024) void k_scan_partials(Axis r, Axis c) {
 
 // Words -> localMap (rank or -1) and globalMap (rank -> global id); the words'
 // counts become global.  A wavefront takes kCompactWords words, lane i id i of
-// each.
+// each.  Only a bad row pointer, which the host refuses after this kernel, flags
+// more ids than gmap has room for (a row counts as used where the pointer
+// increases, whether or not it ends at nnz): those are not stored.
 constexpr int kCompactWords = 16;
 __global__ __launch_bounds__(256) void k_compact(Axis r, Axis c) {
   const Axis& ax = blockIdx.y ? c : r;
@@ -243,7 +246,7 @@ __global__ __launch_bounds__(256) void k_compact(Axis r, Axis c) {
     const int64_t id = (w0 + i) * 64 + lane;
     const bool on = (bits >> lane) & 1ull;
     if (id < ax.range) ax.lmap[id] = on ? rank : -1;
-    if (on) ax.gmap[rank] = ax.lo + id;
+    if (on && rank < ax.cap) ax.gmap[rank] = ax.lo + id;
   }
 }
 
@@ -926,10 +929,12 @@ spc3d_status create_plan(spc3d_plan* out, int64_t nnz, const int64_t* d_row_gid,
   const Axis ax_r{d_rowptr ? nullptr : d_row_gid, row_lo, rr,
                   reinterpret_cast<uint8_t*>(p->lmap_r),
                   reinterpret_cast<RankWord*>(w + L.word_r),
-                  reinterpret_cast<int32_t*>(w + L.partial_r), p->lmap_r, p->gmap_r, small + 0};
+                  reinterpret_cast<int32_t*>(w + L.partial_r), p->lmap_r, p->gmap_r,
+                  nnz < rr ? nnz : rr, small + 0};
   const Axis ax_c{d_col_gid, col_lo, cr, reinterpret_cast<uint8_t*>(p->lmap_c),
                   reinterpret_cast<RankWord*>(w + L.word_c),
-                  reinterpret_cast<int32_t*>(w + L.partial_c), p->lmap_c, p->gmap_c, small + 1};
+                  reinterpret_cast<int32_t*>(w + L.partial_c), p->lmap_c, p->gmap_c,
+                  nnz < cr ? nnz : cr, small + 1};
   int32_t* chunk_row = tmp.counts;   // free until the sort
   st = localize(nnz, ax_r, ax_c, d_rowptr, chunk_row, small + 2, small + 4, stream);
   if (st != SPC3D_OK) return bail(st);
