@@ -160,8 +160,19 @@ __device__ inline void copy_to(float (&a)[NCH][VEC], const float (&b)[NCH][VEC])
     for (int t = 0; t < VEC; ++t) a[ch][t] = b[ch][t];
 }
 
-// Puts (or adds) the finished local row r.  An addition loads all of a lane's
-// vectors before it stores any: vectors of neighbouring lanes may overlap.
+// Where vectors of neighbouring lanes overlap (FULL = false), every lane's loads
+// of a row that is added to come before any lane's stores to it.  A lane's own
+// vectors do not overlap, so only this keeps the compiler from storing one
+// before it loads the next, which may hold elements of the neighbour's.
+template <bool FULL>
+__device__ inline void loads_before_stores() {
+  if constexpr (!FULL) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// Puts (or adds) the finished local row r.
 template <int OUTM, int VEC, int LPN, int NCH, bool FULL>
 __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
                                   const LaneCols<VEC, LPN, NCH, FULL>& lc,
@@ -173,6 +184,7 @@ __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
   } else {
     float v[NCH][VEC];
     get_at<VEC, LPN, NCH, FULL>(row, lc, v);
+    loads_before_stores<FULL>();
     add_to<VEC, NCH>(v, acc);
     put_at<VEC, LPN, NCH, FULL>(row, lc, v);
   }
@@ -298,6 +310,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
           if (!seen) {
             copy_to<VEC, NCH>(lead, acc);
           } else if constexpr (OUTM == kAddSlab) {
+            loads_before_stores<FULL>();
             add_to<VEC, NCH>(acc, pre[u]);
             put_at<VEC, LPN, NCH, FULL>(dst[u], lc, acc);
           } else {
