@@ -176,13 +176,26 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
                       void* d_buf, size_t buf_bytes, hipStream_t stream, const void* d_A,
                       float* d_out, bool static_buf = false) {
   const bool fused = d_A != nullptr;
+  // The shape, and with it the order of every sum, follows from the operands:
+  // the same rows put in Y or added to a slab of any ld and k0 have the same
+  // bits.  The destination's alignment decides only what is refused (rows wider
+  // than the scalar shapes take).
+  const bool al_in = aligned16(d_X) && (!fused || aligned16(d_A));
+  const bool al_out = aligned16(Y.base) && Y.ld % 4 == 0;
+  const auto lds_of = [&](const Shape& s) {
+    return s.window ? size_t(0) : 4 * spmm_wave_lds(s.items, s.lanes, s.nch, s.vec, fused);
+  };
   Shape sh;
-  const bool al = aligned16(d_X) && aligned16(Y.base) && Y.ld % 4 == 0 &&
-                  (!fused || aligned16(d_A));
-  spc3d_status st = pick_shape(kz, x_t, al, variant, fused ? 2 : 1, p->nnz, &sh);
+  spc3d_status st = pick_shape(kz, x_t, al_in && al_out, variant, fused ? 2 : 1, p->nnz, &sh);
   if (st != SPC3D_OK) return st;
+  if (al_in && !al_out) {
+    Shape vec;
+    if (pick_shape(kz, x_t, true, variant, fused ? 2 : 1, p->nnz, &vec) == SPC3D_OK &&
+        lds_of(vec) <= 65536)
+      sh = vec;
+  }
   RunShape rs;
-  const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, al, &rs) &&
+  const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, al_in, &rs) &&
                    buf_bytes >= (size_t)carry_bytes(p->nnz, rs.item(), kz);
   const int64_t nitems = (p->nnz + sh.items - 1) / sh.items;
   const size_t need = (size_t)nitems * 2 * (size_t)kz * 4;
@@ -193,7 +206,7 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
                   "(use spc3d_sddmm_spmm with a caller buffer)", need, buf_bytes);
     return fail(SPC3D_ERR_WORKSPACE, "SpMM buffer %zu bytes < %zu required", buf_bytes, need);
   }
-  const size_t lds = sh.window ? 0 : 4 * spmm_wave_lds(sh.items, sh.lanes, sh.nch, sh.vec, fused);
+  const size_t lds = lds_of(sh);
   if (lds > 65536) return fail(SPC3D_ERR_UNSUPPORTED, "variant needs %zu bytes of LDS", lds);
   DeviceGuard dg;
   st = dg.enter(p);

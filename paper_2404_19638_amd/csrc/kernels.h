@@ -59,7 +59,23 @@ __device__ inline void st_stream(T* p, T v) {
   *p = v;
 #endif
 }
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Four values at an address with the element's alignment (the hardware's
+// 16-byte accesses need no more).
+typedef float f32x4_e4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline f32x4_e4 ld_stream4(const float* p) {
+#if SPC3D_STREAM_HINTS
+  return __builtin_nontemporal_load(reinterpret_cast<const f32x4_e4*>(p));
+#else
+  return *reinterpret_cast<const f32x4_e4*>(p);
+#endif
+}
+__device__ inline void st_stream4(float* p, f32x4_e4 v) {
+#if SPC3D_STREAM_HINTS
+  __builtin_nontemporal_store(v, reinterpret_cast<f32x4_e4*>(p));
+#else
+  *reinterpret_cast<f32x4_e4*>(p) = v;
+#endif
+}
 
 // Row of slot s from the head bitmap.
 __device__ inline int row_of(const uint64_t* __restrict__ head, const int32_t* __restrict__ tile_row,
@@ -216,7 +232,8 @@ __global__ __launch_bounds__(256) void k_sddmm(int64_t nnz, int64_t nitems, int6
 // ------------------------------------------------------------------- SpMM
 
 // Stores (or, with accumulate, adds) this lane's part of a finished row sum
-// at yr, the first element of the destination row.
+// at yr, the first element of the destination row (of any alignment: where a
+// row goes must not decide in which order it is summed).
 template <int VEC, int NCH>
 __device__ inline void store_row_at(float* __restrict__ yr, int nvec, int q, int lpn,
                                     const float (&acc)[NCH][VEC], int accumulate) {
@@ -228,9 +245,9 @@ __device__ inline void store_row_at(float* __restrict__ yr, int nvec, int q, int
       if constexpr (VEC % 4 == 0) {
 #pragma unroll
         for (int t = 0; t < VEC; t += 4) {
-          f32x4 o = {acc[ch][t], acc[ch][t + 1], acc[ch][t + 2], acc[ch][t + 3]};
-          if (accumulate) o = ld_stream(reinterpret_cast<const f32x4*>(y + t)) + o;
-          st_stream(reinterpret_cast<f32x4*>(y + t), o);
+          f32x4_e4 o = {acc[ch][t], acc[ch][t + 1], acc[ch][t + 2], acc[ch][t + 3]};
+          if (accumulate) o = ld_stream4(y + t) + o;
+          st_stream4(y + t, o);
         }
       } else {
 #pragma unroll
@@ -281,7 +298,7 @@ __device__ inline void load_dst(const float* __restrict__ yr, int nvec, int q, i
     if (vi < nvec) {
 #pragma unroll
       for (int t = 0; t < VEC; t += 4) {
-        const f32x4 v = ld_stream(reinterpret_cast<const f32x4*>(yr + vi * VEC + t));
+        const f32x4_e4 v = ld_stream4(yr + vi * VEC + t);
         pre[ch][t] = v.x; pre[ch][t + 1] = v.y; pre[ch][t + 2] = v.z; pre[ch][t + 3] = v.w;
       }
     }
@@ -299,9 +316,9 @@ __device__ inline void store_pre(float* __restrict__ yr, int nvec, int q, int lp
     if (vi < nvec) {
 #pragma unroll
       for (int t = 0; t < VEC; t += 4) {
-        const f32x4 o = {pre[ch][t] + acc[ch][t], pre[ch][t + 1] + acc[ch][t + 1],
+        const f32x4_e4 o = {pre[ch][t] + acc[ch][t], pre[ch][t + 1] + acc[ch][t + 1],
                          pre[ch][t + 2] + acc[ch][t + 2], pre[ch][t + 3] + acc[ch][t + 3]};
-        st_stream(reinterpret_cast<f32x4*>(yr + vi * VEC + t), o);
+        st_stream4(yr + vi * VEC + t, o);
       }
     }
   }

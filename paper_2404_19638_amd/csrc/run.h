@@ -44,7 +44,6 @@ typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_e4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_e2 __attribute__((ext_vector_type(4), aligned(2)));
-typedef float f32x4_e4 __attribute__((ext_vector_type(4), aligned(4)));
 
 struct RunArgs {
   int64_t nnz, nitems, nblocks;
