@@ -131,8 +131,19 @@ int64_t carry_bytes(int64_t nnz, int64_t item, int kz) {
   return (n > 0 ? n : 1) * 2 * kz * 4;
 }
 
+inline int row_bytes(int kz, spc3d_dtype t) { return kz * (t == SPC3D_F32 ? 4 : 2); }
+constexpr int kWholeRow = 512;   // bytes of the widest row that is taken whole
+
+// Scratch of a call through the run family: the carries, and the sums of the
+// dots of a sliced fused pass that adds to out (see run_family).
+int64_t run_bytes(const Plan* p, const RunShape& sh, bool fused, int kz, spc3d_dtype t,
+                  bool acc_out) {
+  const bool sums = fused && acc_out && sh.slices > 1 && row_bytes(kz, t) != kWholeRow;
+  return carry_bytes(p->nnz, sh.item(), kz) + (sums ? 4 * p->nnz : 0);
+}
+
 // Runs the pass through the run family.
-void run_family(const Plan* p, const RunShape& sh, int transpose, const float* d_vals,
+void run_family(const Plan* p, RunShape sh, int transpose, const float* d_vals,
                 const void* d_X, spc3d_dtype t, int kz, const YOut& Y, int acc, float* carry,
                 hipStream_t stream, const void* d_A, float* d_out) {
   Orient o = transpose ? p->csc() : p->csr();
@@ -158,9 +169,22 @@ void run_family(const Plan* p, const RunShape& sh, int transpose, const float* d
       launch_run<bf16_t, 8, false>(sh, a, outm, o.ptr, 0, sh.slices, stream);
     return;
   }
-  // each slice adds its part of the dots to the slices before it
+  a.dots = d_out;
+  if (sh.slices > 1 && a.acc_out) {
+    // out holds what is added to: rows of 512 bytes are taken whole, with the
+    // runs and so the row sums of the slices; the dots of wider ones are summed
+    // behind the carries
+    if (row_bytes(kz, t) == kWholeRow) {
+      sh.slices = 1;
+      sh.kw = kz;
+      sh.nch = kWholeRow / 16 / sh.lanes;
+    } else {
+      a.dots = carry + carry_bytes(p->nnz, sh.item(), kz) / 4;
+    }
+  }
   for (int s = 0; s < sh.slices; ++s) {
-    if (s) a.acc_out = 1;
+    a.part_first = s == 0;
+    a.part_last = s == sh.slices - 1;
     if (t == SPC3D_F32)
       launch_run<float, 4, true>(sh, a, outm, o.ptr, s, 1, stream);
     else
@@ -196,7 +220,7 @@ spc3d_status run_spmm(Plan* p, int transpose, const float* d_vals, const void* d
   }
   RunShape rs;
   const bool run = variant < 0 && pick_run(p, transpose, fused, kz, x_t, al_in, &rs) &&
-                   buf_bytes >= (size_t)carry_bytes(p->nnz, rs.item(), kz);
+                   buf_bytes >= (size_t)run_bytes(p, rs, fused, kz, x_t, (acc & kAccOut) != 0);
   const int64_t nitems = (p->nnz + sh.items - 1) / sh.items;
   const size_t need = (size_t)nitems * 2 * (size_t)kz * 4;
   if (!run && buf_bytes < need) {
@@ -370,7 +394,7 @@ spc3d_status spc3d_spmm_buffer_size(spc3d_plan h, int transpose, int32_t kz, int
       for (int t = 0; t < 2; ++t) {
         RunShape rs;
         if (!pick_run(p, transpose, f != 0, kz, t ? SPC3D_BF16 : SPC3D_F32, false, &rs)) continue;
-        const size_t n = (size_t)carry_bytes(p->nnz, rs.item(), kz);
+        const size_t n = (size_t)run_bytes(p, rs, f != 0, kz, t ? SPC3D_BF16 : SPC3D_F32, true);
         if (n > *bytes) *bytes = n;
       }
   return SPC3D_OK;

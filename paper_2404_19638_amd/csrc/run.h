@@ -62,6 +62,8 @@ struct RunArgs {
   float* carry;
   float* out;                // fused
   int acc_out;
+  float* dots;               // fused, PARTS: sums of the slices before this one
+  int part_first, part_last; // fused, PARTS: this slice is the row's first, last
 };
 
 // Where a finished row goes.
@@ -192,7 +194,11 @@ __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
 // AROW: how the fused pass gets its rows of A.
 enum { kNoA = 0, kEachSlot = 1, kEachRow = 2 };
 
-template <typename T, int VEC, int LPN, int NCH, int U, bool FULL, int AROW, int OUTM>
+// PARTS: a fused pass over one slice of several.  The slices' dots are summed
+// in a.dots, and the last slice multiplies the sum by the entry's value: a
+// product with a part of the dot could overflow, or be infinite with the other
+// sign, where the product with the whole is not.
+template <typename T, int VEC, int LPN, int NCH, int U, bool FULL, int AROW, int OUTM, bool PARTS>
 __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
   constexpr bool FUSED = AROW != kNoA;
   constexpr int G = 64 / LPN;
@@ -337,7 +343,8 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
               const float f = fmaf(av[ch][t], xv[ch][t], d);
               d = (FULL || t >= lc.dup[ch]) ? f : d;
             }
-          d = v * group_sum<LPN>(d);
+          d = group_sum<LPN>(d);
+          if constexpr (!PARTS) d = v * d;
           res = (q == u) ? d : res;
         }
         if (!TAIL || m * U + u < nrun) {
@@ -361,7 +368,15 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (int i = lane; i < (int)(e - b); i += 64) {
-      const float o = __int_as_float(s_val[(i >> a.lg_s) * P + (i & (S - 1))]);
+      float o = __int_as_float(s_val[(i >> a.lg_s) * P + (i & (S - 1))]);
+      if constexpr (PARTS) {
+        if (!a.part_first) o = ld_stream(a.dots + b + i) + o;
+        if (!a.part_last) {
+          st_stream(a.dots + b + i, o);
+          continue;
+        }
+        if (a.vals) o = ld_stream(a.vals + b + i) * o;
+      }
       st_stream(a.out + b + i, a.acc_out ? ld_stream(a.out + b + i) + o : o);
     }
   }
@@ -475,17 +490,27 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
   a.nblocks = (a.nitems + 3) / 4;
   const dim3 grid((unsigned)a.nblocks, (unsigned)ns);
   const size_t lds = (size_t)4 * 4 * run_words(64 / sh.lanes, 1 << sh.lg_s);
-#define SPC3D_RUN_GO(L, N, U, F, M, O)                                                          \
+#define SPC3D_RUN_GO(L, N, U, F, M, O, P)                                                       \
   do {                                                                                          \
-    hipLaunchKernelGGL((k_run<T, VEC, L, N, U, F, M, O>), grid, dim3(256), lds, st, a);          \
+    hipLaunchKernelGGL((k_run<T, VEC, L, N, U, F, M, O, P>), grid, dim3(256), lds, st, a);       \
     hipLaunchKernelGGL((k_run_fixup<VEC, L, N, F, O>), grid, dim3(256), 0, st, a, ptr);          \
   } while (0)
-#define SPC3D_RUN_OUT(L, N, U, F, O)                                        \
-  do {                                                                      \
-    if constexpr (!FUSED) SPC3D_RUN_GO(L, N, U, F, kNoA, O);                \
-    else if constexpr (N > 1) SPC3D_RUN_GO(L, N, U, F, kEachRow, O);        \
-    else if (sh.each_row) SPC3D_RUN_GO(L, N, U, F, kEachRow, O);            \
-    else SPC3D_RUN_GO(L, N, U, F, kEachSlot, O);                            \
+#define SPC3D_RUN_A(L, N, U, F, O, P)                                          \
+  do {                                                                         \
+    if constexpr (!FUSED) SPC3D_RUN_GO(L, N, U, F, kNoA, O, false);            \
+    else if constexpr (N > 1) SPC3D_RUN_GO(L, N, U, F, kEachRow, O, P);        \
+    else if (sh.each_row) SPC3D_RUN_GO(L, N, U, F, kEachRow, O, P);            \
+    else SPC3D_RUN_GO(L, N, U, F, kEachSlot, O, P);                            \
+  } while (0)
+// slices of a fused pass are 8 or 16 vectors, which 8 lanes cover
+#define SPC3D_RUN_OUT(L, N, U, F, O)                                           \
+  do {                                                                         \
+    if constexpr (FUSED && F && L == 8 && N <= 2) {                            \
+      if (sh.slices > 1) SPC3D_RUN_A(L, N, U, F, O, true);                     \
+      else SPC3D_RUN_A(L, N, U, F, O, false);                                  \
+    } else {                                                                   \
+      SPC3D_RUN_A(L, N, U, F, O, false);                                       \
+    }                                                                          \
   } while (0)
 #define SPC3D_RUN_FULL(L, N, U, F)                                      \
   do {                                                                  \
@@ -505,6 +530,7 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 #undef SPC3D_RUN_SHAPE
 #undef SPC3D_RUN_FULL
 #undef SPC3D_RUN_OUT
+#undef SPC3D_RUN_A
 #undef SPC3D_RUN_GO
 }
 
