@@ -551,21 +551,39 @@ __global__ __launch_bounds__(256) void k_build_slots(int64_t nnz, int64_t nrows,
 constexpr int kCsrChunk = 512;   // entries of a wavefront of k_csr_rows
 
 // Checks the row pointer, flags the rows with entries and notes the row of
-// every kCsrChunk-th entry.
+// every kCsrChunk-th entry: rows over more than kCsrMany chunks one after
+// another by the whole wavefront.  (One thread a row, one row of 30M entries took
+// 3233 us for the whole setup, 1786 so; the same entries searched one by one
+// 2698.)
+constexpr int kCsrMany = 8;
 __global__ void k_csr_flags(int64_t n, const int64_t* __restrict__ rowptr, int64_t nnz,
                             uint8_t* __restrict__ flag, int32_t* __restrict__ chunk_row,
                             int32_t* __restrict__ err) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i <= n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t v = rowptr[i];
-    const int64_t next = i < n ? rowptr[i + 1] : v;
-    const bool bad = (i == 0 && v != 0) || (i == n && v != nnz) || next < v || v < 0 || v > nnz;
-    if (bad) err[0] = 1;
-    if (i < n) {
-      flag[i] = next > v;
-      if (!bad && next <= nnz)
-        for (int64_t c = (v + kCsrChunk - 1) / kCsrChunk; c * kCsrChunk < next; ++c)
-          chunk_row[c] = (int32_t)i;
+  const int lane = threadIdx.x & 63;
+  for (int64_t i0 = blockIdx.x * (int64_t)blockDim.x + (threadIdx.x & ~63); i0 <= n;
+       i0 += (int64_t)gridDim.x * blockDim.x) {   // uniform per wavefront
+    const int64_t i = i0 + lane;
+    int64_t c = 0, ce = 0;   // the chunks whose first entry is row i's
+    if (i <= n) {
+      const int64_t v = rowptr[i];
+      const int64_t next = i < n ? rowptr[i + 1] : v;
+      const bool bad = (i == 0 && v != 0) || (i == n && v != nnz) || next < v || v < 0 || v > nnz;
+      if (bad) err[0] = 1;
+      if (i < n) {
+        flag[i] = next > v;
+        if (!bad && next <= nnz) {
+          c = (v + kCsrChunk - 1) / kCsrChunk;
+          ce = (next + kCsrChunk - 1) / kCsrChunk;
+        }
+      }
+    }
+    const bool many = ce - c > kCsrMany;
+    if (!many)
+      for (; c < ce; ++c) chunk_row[c] = (int32_t)i;
+    for (uint64_t left = __ballot(many); left; left &= left - 1) {
+      const int l = __ffsll((unsigned long long)left) - 1;
+      const int64_t to = __shfl(ce, l);
+      for (int64_t k = __shfl(c, l) + lane; k < to; k += 64) chunk_row[k] = (int32_t)(i0 + l);
     }
   }
 }
