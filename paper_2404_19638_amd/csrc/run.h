@@ -82,8 +82,10 @@ __device__ inline void read_words(const int32_t* p, int32_t (&o)[U]) {
       const i32x4 c = *reinterpret_cast<const i32x4*>(p + u);
       o[u] = c.x; o[u + 1] = c.y; o[u + 2] = c.z; o[u + 3] = c.w;
     }
+  } else if constexpr (U == 1) {
+    o[0] = p[0];
   } else {
-    static_assert(U == 2, "steps of 2 or a multiple of 4 slots");
+    static_assert(U == 2, "steps of 1, 2 or a multiple of 4 slots");
     const i32x2 c = *reinterpret_cast<const i32x2*>(p);
     o[0] = c.x; o[1] = c.y;
   }
@@ -173,7 +175,12 @@ __device__ inline void loads_before_stores() {
   }
 }
 
-// Puts (or adds) the finished local row r.
+// Puts (or adds) the finished local row r.  What a row is added to is read
+// here, where the row ends.  Read a step ahead, with the gathered rows, it held
+// U rows more in registers, which cost more wavefronts than the wait (folded
+// pass, us, step ahead / here: FP32 kz = 32, R-MAT 2^19, 13.6M entries, 251 / 197,
+// 5.5M banded 169 / 128; kz = 60, R-MAT 2^17, 3.4M, 156 / 132; bfloat16 kz = 128,
+// 3.4M, 288 / 184).
 template <int OUTM, int VEC, int LPN, int NCH, bool FULL>
 __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
                                   const LaneCols<VEC, LPN, NCH, FULL>& lc,
@@ -256,19 +263,6 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
     const int steps = S / U;
     uint4 acur[AROW == kEachRow ? NCH : 1];   // the current row of A
     if constexpr (AROW == kEachRow) load_at<T, VEC, LPN, NCH, FULL>(A, aoff, lc, acur);
-    // kAddSlab: the destination rows of the rows that end in a step, looked up
-    // in the map one step ahead, and loaded with the step's gathered rows.
-    int64_t nmap[OUTM == kAddSlab ? U : 1];
-    auto look_up = [&](uint32_t ends, int rr) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if ((ends >> u) & 1u) {
-          nmap[u] = a.Y.map[rr];
-          ++rr;
-        }
-      }
-    };
-    if constexpr (OUTM == kAddSlab) look_up((uint32_t)run & ((1u << U) - 1u), r);
     for (int m = 0; m < steps; ++m) {
       int32_t col[U], vb[U];
       read_words<U>(s_col + g * P + m * U, col);
@@ -293,18 +287,6 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
           }
         }
       }
-      float pre[OUTM == kAddSlab ? U : 1][NCH][VEC];
-      float* dst[OUTM == kAddSlab ? U : 1];
-      if constexpr (OUTM == kAddSlab) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          if ((hb >> u) & 1u) {
-            dst[u] = a.Y.base + (nmap[u] - a.Y.lo) * a.Y.ld + k0;
-            get_at<VEC, LPN, NCH, FULL>(dst[u], lc, pre[u]);
-          }
-        }
-        if (m + 1 < steps) look_up((uint32_t)run & ((1u << U) - 1u), r + __popc(hb));
-      }
       float res = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -312,15 +294,10 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
         float xv[NCH][VEC];
         unpack_raw<T, VEC, NCH>(x[u], xv);
         if ((hb >> u) & 1u) {   // the row before this slot is complete
-          if (!seen) {
-            copy_to<VEC, NCH>(lead, acc);
-          } else if constexpr (OUTM == kAddSlab) {
-            loads_before_stores<FULL>();
-            add_to<VEC, NCH>(acc, pre[u]);
-            put_at<VEC, LPN, NCH, FULL>(dst[u], lc, acc);
-          } else {
+          if (seen)
             finish_row<OUTM, VEC, LPN, NCH, FULL>(a, r, k0, lc, acc);
-          }
+          else
+            copy_to<VEC, NCH>(lead, acc);
           zero(acc);
           if constexpr (AROW == kEachRow) {
 #pragma unroll
@@ -505,7 +482,7 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 // slices of a fused pass are 8 or 16 vectors, which 8 lanes cover
 #define SPC3D_RUN_OUT(L, N, U, F, O)                                           \
   do {                                                                         \
-    if constexpr (FUSED && F && L == 8 && N <= 2) {                            \
+    if constexpr (FUSED && (F || (VEC == 8 && N == 2 && O != kPut)) && L == 8 && N <= 2) {                            \
       if (sh.slices > 1) SPC3D_RUN_A(L, N, U, F, O, true);                     \
       else SPC3D_RUN_A(L, N, U, F, O, false);                                  \
     } else {                                                                   \
@@ -518,15 +495,21 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
     else if (outm == kAddPacked) SPC3D_RUN_OUT(L, N, U, F, kAddPacked); \
     else if constexpr (FUSED) SPC3D_RUN_OUT(L, N, U, F, kAddSlab);      \
   } while (0)
-#define SPC3D_RUN_SHAPE(L, N, U)                \
-  if (sh.lanes == L && sh.nch == N) {           \
-    if (sh.full) SPC3D_RUN_FULL(L, N, U, true); \
-    else SPC3D_RUN_FULL(L, N, U, false);        \
+// Steps of 2 slots with two vectors a lane and of 1 with four: with steps twice
+// as long two wavefronts a SIMD fewer fit (us, steps of 4 / 2, R-MAT 2^17, 3.4M
+// entries: bfloat16 kz = 128 fused 107 / 104, folded 184 / 157; FP32 kz = 40
+// folded 123 / 115; of 2 / 1, FP32 kz = 128 folded 231 / 178).  Adding, two
+// bfloat16 vectors a lane take the general form, which fits 128 registers where
+// the full one takes 129 (folded 156 / 130).
+#define SPC3D_RUN_SHAPE(L, N, U)                                                    \
+  if (sh.lanes == L && sh.nch == N) {                                               \
+    if (sh.full && !(VEC == 8 && N == 2 && outm != kPut)) SPC3D_RUN_FULL(L, N, U, true); \
+    else SPC3D_RUN_FULL(L, N, U, false);                                            \
   }
   SPC3D_RUN_SHAPE(4, 1, 4)
   SPC3D_RUN_SHAPE(8, 1, 4)
-  SPC3D_RUN_SHAPE(8, 2, 4)
-  SPC3D_RUN_SHAPE(8, 4, 2)
+  SPC3D_RUN_SHAPE(8, 2, 2)
+  SPC3D_RUN_SHAPE(8, 4, 1)
 #undef SPC3D_RUN_SHAPE
 #undef SPC3D_RUN_FULL
 #undef SPC3D_RUN_OUT
