@@ -25,23 +25,42 @@ namespace spc3d {
 
 constexpr int kBatch = 2;
 
-// What bounds both: the slab rows, which are read once from HBM, through an
-// Infinity Cache full of the step's other data.  Reading them nontemporal
-// keeps them from evicting it: an R-MAT share's gather (115 MB) takes 25.8 us
-// against 36.5 after 400 MB of other writes.  Nontemporal stores of what the
-// next kernels read again pay only once it outgrows the caches: packed rows
-// beyond 128 MB (uniform share, 229 MB an operand, whole step 418 to 409 us;
-// R-MAT share, 55 MB, 167 to 169) and slab rows as far (banded bfloat16, 537 MB,
-// 823 to 784).  Slab rows that a scatter adds to are read nontemporal beyond
-// 32 MB (R-MAT share 55 MB 176 to 165; 2^18 rows kz = 30, 18 MB, 166.5 to 169);
-// stored nontemporal at that size too, the next scatter's reads miss: 36.4
-// against 31.8 us where the same slab is added to again.  Before, one 16-byte
-// chunk a thread at cached accesses, or one element a thread where the width or
-// an address was not a multiple of 16 bytes (whole step, before and after: R-MAT
-// share 173 to 167, uniform 416 to 409, banded bfloat16 820 to 781, kz = 30 182
-// to 167).
+// What bounds both: the slab rows, which come from HBM through an Infinity
+// Cache (256 MB) full of the step's other data.  Nontemporal accesses keep what
+// is not read again from evicting the rest; where a step's data fits, they only
+// lose what the cache would have kept.  So each hint has its own line.  us for a
+// whole step (both gathers, the pass, the scatter-reduce; inputs that change
+// between steps), MI355X:
+//
+// kStreamSource, nontemporal loads of a gather, by the bytes of the source rows
+// (cached / nontemporal): R-MAT 2^17, 10 MB 55.3 / 55.9, 18 MB 99.7 / 97.2, 36 MB
+// 151 / 149; R-MAT share, 55 MB 180 / 171, 110 MB 326 / 305; uniform, 28 MB 134 /
+// 131.5.  A conversion to bfloat16 reads 32 bytes a lane in two loads, the second
+// from a line that a nontemporal first one need not leave behind: 5 MB 61.5 / 63.4,
+// 19 MB 73.6 / 76.7, 38 MB 120 / 116.
+//
+// kStreamPacked, nontemporal stores of packed rows, which the pass reads next
+// (cached / nontemporal): 229 MB uniform share 418 / 409, 55 MB R-MAT share 167 /
+// 169.  Rows that are not whole lines gain earlier (kStreamPackedRagged): R-MAT
+// share kz = 40 (69 MB) 295 / 289, 60 (103 MB) 430 / 400, banded kz = 24 (67 MB)
+// 302 / 292, 40 (112 MB) 402 / 369; 24 (41 MB) 222 / 227; of whole lines, 64 (110
+// MB) 305 / 314.
+//
+// kStreamSlab, nontemporal loads of the slab rows a scatter adds to, and
+// kStreamSlabStored, of the stores as well (cached / loads / both): R-MAT share, 55 MB
+// 179 / 171 / 172, 220 MB 586 / 585 / 596; banded, 179 MB 395 / 395 / 386, 268 MB
+// 583 / 585 / 573, 537 MB 828 / 831 / 792; 18 MB 172 / 175 / 174.  What is stored
+// cached the next scatter into the same slab may find there: 55 MB 31.8 us against
+// 36.4, 220 MB 113 against 126.  Slab rows that are not whole 64-byte granules
+// (kz, k0 or ld no multiple of 16, or an address) stay cached: a granule that
+// two rows share is then read or written twice (kz = 24, 41 MB 219 / 223 / 226; kz =
+// 60, 103 MB 387 / 400 / 417; banded, 168 MB 510 / 533 / 536).
+constexpr int64_t kStreamSource = 12 << 20;
+constexpr int64_t kStreamSourceConverted = 32 << 20;
 constexpr int64_t kStreamPacked = 128 << 20;
+constexpr int64_t kStreamPackedRagged = 64 << 20;
 constexpr int64_t kStreamSlab = 32 << 20;
+constexpr int64_t kStreamSlabStored = 256 << 20;
 
 typedef uint32_t vec4u_e4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t vec4u_e2 __attribute__((ext_vector_type(4), aligned(2)));
@@ -74,7 +93,7 @@ struct ChunkAt {
 };
 
 // packed[l*kz + k] = conv(src[(gmap[l]-lo)*ld + k0 + k]).
-template <typename Tin, typename Tout, bool NT>
+template <typename Tin, typename Tout, bool NTLD, bool NTST>
 __global__ __launch_bounds__(256) void k_gather(int64_t n, int rpw, int c, uint32_t magic,
                                                 const int64_t* __restrict__ gmap, int64_t lo,
                                                 const Tin* __restrict__ src, int64_t ld, int k0,
@@ -96,7 +115,7 @@ __global__ __launch_bounds__(256) void k_gather(int64_t n, int rpw, int c, uint3
       const ChunkAt ch(j, c, magic, VO, kz);
       const VI* s = reinterpret_cast<const VI*>(src + __shfl(rg.off, ch.l) + ch.e);
 #pragma unroll
-      for (int h = 0; h < NL; ++h) v[i][h] = __builtin_nontemporal_load(s + h);
+      for (int h = 0; h < NL; ++h) v[i][h] = NTLD ? __builtin_nontemporal_load(s + h) : s[h];
       at[i] = ch.l * kz + ch.e;
     }
 #pragma unroll
@@ -113,7 +132,7 @@ __global__ __launch_bounds__(256) void k_gather(int64_t n, int rpw, int c, uint3
         }
       }
       VOUT* d = reinterpret_cast<VOUT*>(out + at[i]);
-      if constexpr (NT)
+      if constexpr (NTST)
         __builtin_nontemporal_store(o, d);
       else
         *d = o;
@@ -231,12 +250,16 @@ void launch_gather(int64_t n, const int64_t* gmap, int64_t lo, const void* src, 
     return;
   }
   const RowSplit sp(n, kz, VO);
-  if (n * kz * (int64_t)sizeof(Tout) > kStreamPacked)
-    hipLaunchKernelGGL((k_gather<Tin, Tout, true>), sp.grid, dim3(256), 0, stream, n, sp.rpw, sp.c,
-                       sp.magic, gmap, lo, s, ld, k0, kz, d);
-  else
-    hipLaunchKernelGGL((k_gather<Tin, Tout, false>), sp.grid, dim3(256), 0, stream, n, sp.rpw,
-                       sp.c, sp.magic, gmap, lo, s, ld, k0, kz, d);
+  const int64_t from = n * kz * (int64_t)sizeof(Tin), to = n * kz * (int64_t)sizeof(Tout);
+  const bool ntld = from > (sizeof(Tin) == sizeof(Tout) ? kStreamSource : kStreamSourceConverted);
+  const bool ntst = to > (kz * sizeof(Tout) % 128 ? kStreamPackedRagged : kStreamPacked);
+#define SPC3D_GATHER(LD, ST)                                                                      \
+  hipLaunchKernelGGL((k_gather<Tin, Tout, LD, ST>), sp.grid, dim3(256), 0, stream, n, sp.rpw,     \
+                     sp.c, sp.magic, gmap, lo, s, ld, k0, kz, d)
+  if (ntld && ntst) SPC3D_GATHER(true, true);   // rows to store this way are many enough to load so
+  else if (ntld) SPC3D_GATHER(true, false);
+  else SPC3D_GATHER(false, false);
+#undef SPC3D_GATHER
 }
 
 }  // namespace
@@ -306,8 +329,10 @@ spc3d_status spc3d_scatter_reduce(spc3d_plan h, spc3d_axis axis, const float* d_
                        gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
   } else {
     const RowSplit sp(n, kz, 4);
-    const int64_t bytes = n * kz * 4;
-    if (bytes > kStreamPacked)
+    const bool granules = ((kz | k0 | ld_dst) & 15) == 0 &&
+                          (reinterpret_cast<uintptr_t>(d_dst) & 63u) == 0;
+    const int64_t bytes = granules ? n * kz * 4 : 0;
+    if (bytes > kStreamSlabStored)
       hipLaunchKernelGGL((k_scatter_add<true, true>), sp.grid, dim3(256), 0, stream, n, sp.rpw,
                          sp.c, sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
     else if (bytes > kStreamSlab)
