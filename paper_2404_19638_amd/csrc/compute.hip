@@ -71,7 +71,17 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // 63.8 at 9.5 entries, kz = 32), except at 4 vectors a lane (banded, 12
 // entries, kz = 128 524 / 574).  Below about 7000 wavefronts (7 per SIMD) the
 // shorter run is faster: R-MAT 2^16, kz = 32 at 16 / 32 / 64 slots 34.6 / 28.2 /
-// 33.6, 2^15 20.8 / 21.9 / 24.8.
+// 33.6, 2^15 20.8 / 21.9 / 24.8.  Small blocks take runs of 8 and 4 slots: with
+// runs of 16 there were too few wavefronts, and each walks its run from one
+// memory round trip to the next (SpMM, us, the shapes before the run family /
+// runs of 16 / 8 / 4: FP32 kz = 16 40,000 entries 6.6 / 7.9 / 6.7 / 6.2, 148,000
+// 7.5 / 9.3 / 7.8 / 7.4, 298,670 9.8 / 10.8 / 8.8 / 9.0, 704,939 15.6 / 14.1 / 12.9
+// / 16.1, 1.6M 31.2 / 20.7 / 22.9; kz = 32 40,000 6.9 / 7.5 / 6.5 / 6.4, 298,670
+// 12.4 / 10.1 / 9.9, 401,951 12.9 / 11.1 / 11.4; kz = 128 106,242 19.3 / 15.3 /
+// 15.0 / 17.9, 235,037 16.4 / 15.0 / 16.1).  Groups of 4 lanes, whose items are
+// twice as long, change at more wavefronts, and stop at 32: with 64 an item's
+// indices take 35 KB of LDS, four blocks a CU (kz = 16, 13.6M entries, runs of 32
+// / 64 125 / 154).
 //
 // With two or more vectors a lane the SpMM takes 64 from 4000 wavefronts on
 // (R-MAT 2^18, degree 12, kz = 96 101 / 98; uniform, 3M entries, kz = 128 218 /
@@ -122,7 +132,13 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);
   const int64_t from64 = (fused ? sh->nch == 4 : sh->nch >= 2) ? 4000 : 7000;
   const int64_t from32 = !fused && sh->nch >= 2 ? 6000 : 7000;
-  sh->lg_s = long_runs && p->nnz >= from64 * 64 * G ? 6 : p->nnz >= from32 * 32 * G ? 5 : 4;
+  const int64_t from16 = sh->lanes == 4 ? 4000 : sh->nch >= 2 ? 1800 : 2500;
+  const int64_t from8 = sh->lanes == 4 ? 1500 : 1000;
+  sh->lg_s = long_runs && sh->lanes == 8 && p->nnz >= from64 * 64 * G ? 6
+             : p->nnz >= from32 * 32 * G                            ? 5
+             : p->nnz >= from16 * 16 * G                            ? 4
+             : p->nnz >= from8 * 8 * G                              ? 3
+                                                                    : 2;
   return true;
 }
 
