@@ -99,6 +99,13 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // degree 24, 66.2 / 70.8; banded kz = 96 197 / 230, though 2^18, degree 32, 165 /
 // 157).
 //
+// Destinations ahead.  Adding to a slab whose rows come from HBM, on rows so short
+// that nearly every step ends some, a destination read where its row ends is
+// waited for each time; read where the row starts it costs a row of registers
+// (folded, us, at the end / at the start: uniform, 4.0M entries, 2.2 a row, FP32
+// kz = 16 213 / 206, 32 262 / 252, 64 512 / 480, bfloat16 64 372 / 363; slab rows
+// within the caches: banded, 900,000 entries, kz = 16 26 / 36, kz = 32 39 / 50).
+//
 // Rows of A.  With one vector a lane, loading the slot's row of A for every
 // slot (from L1 mostly) costs less than loading it under a mask where a row
 // starts, unless rows are long: 79.6 against 84.2 us on the 2^24-vertex share
@@ -128,6 +135,7 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
     if (wide_bf16 && !fused && sh->slices == 1 && p->nnz >= (int64_t(1) << 21)) return false;
   }
   sh->each_row = len16;
+  sh->ahead = p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
   const int64_t G = 64 / sh->lanes;
   const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);
   const int64_t from64 = (fused ? sh->nch == 4 : sh->nch >= 2) ? 4000 : 7000;

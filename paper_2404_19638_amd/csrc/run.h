@@ -201,11 +201,15 @@ __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
 // AROW: how the fused pass gets its rows of A.
 enum { kNoA = 0, kEachSlot = 1, kEachRow = 2 };
 
+// AHEAD: what a row is added to is read where the row starts, its map entry a row
+// before that, instead of where it ends (see pick_run).
+//
 // PARTS: a fused pass over one slice of several.  The slices' dots are summed
 // in a.dots, and the last slice multiplies the sum by the entry's value: a
 // product with a part of the dot could overflow, or be infinite with the other
 // sign, where the product with the whole is not.
-template <typename T, int VEC, int LPN, int NCH, int U, bool FULL, int AROW, int OUTM, bool PARTS>
+template <typename T, int VEC, int LPN, int NCH, int U, bool FULL, int AROW, int OUTM, bool PARTS,
+          bool AHEAD>
 __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
   constexpr bool FUSED = AROW != kNoA;
   constexpr int G = 64 / LPN;
@@ -255,6 +259,34 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
   float acc[NCH][VEC], lead[NCH][VEC];
   zero(acc);
   zero(lead);
+  // AHEAD: the destination of row r, what it held, and where row r + 1 goes
+  float* dst = nullptr;
+  float held[NCH][VEC];
+  int64_t next = 0;
+  auto place_of = [&](int rr) {
+    if constexpr (OUTM == kAddSlab)
+      next = rr < (int)a.Y.n ? a.Y.map[rr] - a.Y.lo : 0;
+    else
+      next = rr;
+  };
+  auto start_row = [&]() {   // row r, whose place was looked up
+    dst = a.Y.base + next * a.Y.ld + k0;
+    get_at<VEC, LPN, NCH, FULL>(dst, lc, held);
+    place_of(r + 1);
+  };
+  auto end_row = [&]() {
+    if constexpr (AHEAD) {
+      loads_before_stores<FULL>();
+      add_to<VEC, NCH>(acc, held);
+      put_at<VEC, LPN, NCH, FULL>(dst, lc, acc);
+    } else {
+      finish_row<OUTM, VEC, LPN, NCH, FULL>(a, r, k0, lc, acc);
+    }
+  };
+  if constexpr (AHEAD) {
+    place_of(first ? r : r + 1);
+    if (first) start_row();
+  }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
@@ -295,7 +327,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
         unpack_raw<T, VEC, NCH>(x[u], xv);
         if ((hb >> u) & 1u) {   // the row before this slot is complete
           if (seen)
-            finish_row<OUTM, VEC, LPN, NCH, FULL>(a, r, k0, lc, acc);
+            end_row();
           else
             copy_to<VEC, NCH>(lead, acc);
           zero(acc);
@@ -305,6 +337,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
           }
           ++r;
           seen = true;
+          if constexpr (AHEAD) start_row();
         }
         if constexpr (FUSED) {
           float av[NCH][VEC];
@@ -382,7 +415,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
     // the run's last row, with the runs it continues into
     if (has_next) add_to<VEC, NCH>(acc, nx);
     if (nF || ends_at_e)
-      finish_row<OUTM, VEC, LPN, NCH, FULL>(a, r, k0, lc, acc);
+      end_row();
     else
       put_at<VEC, LPN, NCH, FULL>(carry + kz, lc, acc);
   }
@@ -453,6 +486,7 @@ struct RunShape {
   int kw, slices;    // elements per slice, slices of a row
   bool full;         // lanes cover a slice exactly
   bool each_row;     // fused: a row of A is loaded where it starts, not for every slot
+  bool ahead;        // adding: a row's destination is read where the row starts
   int64_t item() const { return (64 / lanes) << lg_s; }
 };
 
@@ -467,17 +501,26 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
   a.nblocks = (a.nitems + 3) / 4;
   const dim3 grid((unsigned)a.nblocks, (unsigned)ns);
   const size_t lds = (size_t)4 * 4 * run_words(64 / sh.lanes, 1 << sh.lg_s);
-#define SPC3D_RUN_GO(L, N, U, F, M, O, P)                                                       \
+#define SPC3D_RUN_GO(L, N, U, F, M, O, P, H)                                                    \
   do {                                                                                          \
-    hipLaunchKernelGGL((k_run<T, VEC, L, N, U, F, M, O, P>), grid, dim3(256), lds, st, a);       \
+    hipLaunchKernelGGL((k_run<T, VEC, L, N, U, F, M, O, P, H>), grid, dim3(256), lds, st, a);    \
     hipLaunchKernelGGL((k_run_fixup<VEC, L, N, F, O>), grid, dim3(256), 0, st, a, ptr);          \
+  } while (0)
+#define SPC3D_RUN_H(L, N, U, F, M, O, P)                                       \
+  do {                                                                         \
+    if constexpr (O == kAddSlab && F && !P && N * VEC <= 8) {                  \
+      if (sh.ahead) SPC3D_RUN_GO(L, N, U, F, M, O, P, true);                   \
+      else SPC3D_RUN_GO(L, N, U, F, M, O, P, false);                           \
+    } else {                                                                   \
+      SPC3D_RUN_GO(L, N, U, F, M, O, P, false);                                \
+    }                                                                          \
   } while (0)
 #define SPC3D_RUN_A(L, N, U, F, O, P)                                          \
   do {                                                                         \
-    if constexpr (!FUSED) SPC3D_RUN_GO(L, N, U, F, kNoA, O, false);            \
-    else if constexpr (N > 1) SPC3D_RUN_GO(L, N, U, F, kEachRow, O, P);        \
-    else if (sh.each_row) SPC3D_RUN_GO(L, N, U, F, kEachRow, O, P);            \
-    else SPC3D_RUN_GO(L, N, U, F, kEachSlot, O, P);                            \
+    if constexpr (!FUSED) SPC3D_RUN_H(L, N, U, F, kNoA, O, false);             \
+    else if constexpr (N > 1) SPC3D_RUN_H(L, N, U, F, kEachRow, O, P);         \
+    else if (sh.each_row) SPC3D_RUN_H(L, N, U, F, kEachRow, O, P);             \
+    else SPC3D_RUN_H(L, N, U, F, kEachSlot, O, P);                             \
   } while (0)
 // slices of a fused pass are 8 or 16 vectors, which 8 lanes cover
 #define SPC3D_RUN_OUT(L, N, U, F, O)                                           \
@@ -514,6 +557,7 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 #undef SPC3D_RUN_FULL
 #undef SPC3D_RUN_OUT
 #undef SPC3D_RUN_A
+#undef SPC3D_RUN_H
 #undef SPC3D_RUN_GO
 }
 
