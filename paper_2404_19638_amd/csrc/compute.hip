@@ -25,6 +25,14 @@ extern template void launch_run<bf16_t, 8, false>(SPC3D_RUN_LAUNCH_ARGS);
 
 namespace {
 
+// The entries use fewer rows of the gathered table than entries at uniform
+// positions would (0.8 of the expected number).
+bool skewed(const Plan* p, int transpose) {
+  const int64_t rows = transpose ? p->R : p->C;
+  const double ids = transpose ? (double)(p->row_hi - p->row_lo) : (double)(p->col_hi - p->col_lo);
+  return rows < 0.8 * ids * -expm1(-(double)p->nnz / ids);
+}
+
 // Slices of a packed row that a pass takes one after another (1: the whole
 // row).  A pass over a large table is bound by the row lines that miss L2 (they
 // arrive at 6.5 to 7.5 TB/s from the Infinity Cache and HBM alike).  Where
@@ -36,18 +44,14 @@ namespace {
 // 569; 2^18 kz = 128 (85 MB) 340 / 277 / 278, kz = 64 (42 MB) 141 / - / 145;
 // 2^17 kz = 128 (44 MB) 147 / 126 / 140, kz = 64 72 / - / 76.  Uniform
 // columns do not gain: 2^20 columns, 32 entries each, kz = 64 1248 / - / 1344.
-// So only blocks whose entries use fewer columns than uniform positions would
-// (0.8 of the expected number) are sliced.  The fused pass reads A and adds to
+// So only skewed blocks are sliced.  The fused pass reads A and adds to
 // the dots once more per slice, so it slices only rows of 512 bytes or more of
 // tables beyond 128 MB: R-MAT 2^20 kz = 128 1867 / 1662 / 1712, 2^19 833 /
 // 767 / 874, 2^18 372 / 368 / 451, kz = 64 2^20 820 / - / 829; at kz = 96, three
-// slices of 128 bytes, 2^20 vertices of degree 8 took 449 against 401.  Nor does it
-// slice rows below 20 entries: the 2^24-vertex share (9.3), kz = 128, 318 whole /
-// 340, the step with the scatter folded in 531 / 606.
+// slices of 128 bytes, 2^20 vertices of degree 8 took 449 against 401.
 int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
   const int64_t rows = transpose ? p->R : p->C;   // of the gathered table
-  const double ids = transpose ? (double)(p->row_hi - p->row_lo) : (double)(p->col_hi - p->col_lo);
-  if (row_bytes % 128 || rows >= 0.8 * ids * -expm1(-(double)p->nnz / ids)) return 1;
+  if (row_bytes % 128 || !skewed(p, transpose)) return 1;
   const int64_t lines = row_bytes / 128, table = rows * row_bytes;
   constexpr int64_t MB = 1 << 20;
   if (lines < (fused ? 4 : 2)) return 1;
@@ -89,15 +93,31 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // pass 64 from 4000 at four vectors (uniform, 3M, kz = 128 232 / 225).
 //
 // Left to the shapes of pick_shape from 2^17 entries on, where those read whole
-// vectors (vec_ok: the operands' alignment; us there / here): four vectors a lane on
-// short rows, whose row ends cost more than the steps between them (SpMM
-// below 10 entries a row: banded, 7, kz = 96 32.6 / 33.8, uniform, 4, 62.8 /
-// 64.6; fused below 20: uniform, 4, kz = 96 75.6 / 82.1, banded, 12, 40,000
-// rows, kz = 128 28.2 / 30.7); bfloat16 rows of 256 bytes, fused, below 5 entries
-// (uniform, 4, 67.3 / 71.6); and in the SpMM from 2^21 entries on, where
-// pick_shape's items of 512 slots begin (R-MAT 2^18, degree 12, 76.0 / 79.7; 2^17,
-// degree 24, 66.2 / 70.8; banded kz = 96 197 / 230, though 2^18, degree 32, 165 /
-// 157).
+// vectors (vec_ok: the operands' alignment; us there / here):
+// - four vectors a lane on short rows, whose row ends cost more than the steps
+//   between them: SpMM below 10 entries a row (banded, 7, kz = 96 32.6 / 33.8,
+//   uniform, 4, 62.8 / 64.6), fused below 20 (uniform, 4, kz = 96 75.6 / 82.1,
+//   banded, 12, 40,000 rows, kz = 128 28.2 / 30.7);
+// - four bfloat16 vectors a lane, which take 185 registers: the fused pass (kz =
+//   256, uniform, 401,951 entries, 0.83 times as fast, R-MAT 2^16, 1.6M, 0.85,
+//   folded 0.91 and 0.86), and SpMM but on skewed columns (uniform 0.88, R-MAT
+//   1.07);
+// - two bfloat16 vectors a lane: fused below 5 entries a row (uniform, 4, 67.3 /
+//   71.6), SpMM from 2^21 entries on, where pick_shape's items of 512 slots begin
+//   (R-MAT 2^18, degree 12, 76.0 / 79.7; 2^17, degree 24, 66.2 / 70.8; banded kz =
+//   96 197 / 230, though 2^18, degree 32, 165 / 157), and between 2^19 and 2^20, but
+//   on skewed columns (kz = 96, uniform 632,099 23.4 / 25.0, banded 704,939 26.5 /
+//   28.2; R-MAT 999,239 39.0 / 34.5).
+//
+// Slices of the fused pass.  Each ends every row again, so rows below a number of
+// entries are taken whole (us, the plain and the folded pass, whole / sliced).
+// Rows of 512 bytes, 36 entries: FP32, R-MAT 2^19 at 25 entries a row 391 / 409
+// and 445 / 518, 33 529 / 531 and 578 / 635, 42 718 / 696 and 766 / 799; 2^20 at
+// 39 1366 / 1305 and 1427 / 1426, 49 1860 / 1664 and 1914 / 1787; bfloat16, which
+// goes to pick_shape below, 2^19 at 25 550 / 488 and 602 / 674, 2^20 at 39 1672 /
+// 1433 and 1785 / 1793; the share at 9.3, FP32, 318 / 340.  Wider ones, 28, left to
+// pick_shape below: kz = 192, 2^20 at 24 1187 / 1107 and 1258 / 1316, 29 1536 / 1399
+// and 1616 / 1583.
 //
 // Destinations ahead.  Adding to a slab whose rows come from HBM, on rows so short
 // that nearly every step ends some, a destination read where its row ends is
@@ -120,7 +140,9 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   if (kz < sh->vec || most >= (1 << 24) || most * kz * esz >= (int64_t(1) << 32)) return false;
   const int64_t rows = transpose ? p->C : p->R;
   // a slice of a fused pass ends every row again, and reads its row of A
-  sh->slices = fused && p->nnz < 20 * rows ? 1 : slice_count(p, transpose, fused, (int64_t)kz * esz);
+  const int64_t entries = kz * esz > 512 ? 28 : 36;
+  sh->slices =
+      fused && p->nnz < entries * rows ? 1 : slice_count(p, transpose, fused, (int64_t)kz * esz);
   sh->kw = kz / sh->slices;
   const int nvec = (sh->kw + sh->vec - 1) / sh->vec;
   if (nvec < 3 || nvec > 32) return false;
@@ -129,10 +151,14 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   sh->full = sh->kw == sh->lanes * sh->nch * sh->vec;
   const bool len16 = p->nnz >= 16 * rows;
   if (vec_ok && kz % sh->vec == 0 && p->nnz >= (int64_t(1) << 17)) {
-    const bool wide_bf16 = t == SPC3D_BF16 && sh->nch == 2;
+    const int64_t halves = p->nnz >> 19;   // of 2^20 entries
     if (sh->nch == 4 && p->nnz < (fused ? 20 : 10) * rows) return false;
-    if (wide_bf16 && fused && p->nnz < 5 * rows) return false;
-    if (wide_bf16 && !fused && sh->slices == 1 && p->nnz >= (int64_t(1) << 21)) return false;
+    if (t == SPC3D_BF16 && sh->nch == 4 && (fused || !skewed(p, transpose))) return false;
+    if (t == SPC3D_BF16 && sh->nch == 2) {
+      if (fused && p->nnz < 5 * rows) return false;
+      if (!fused && sh->slices == 1 &&
+          (halves >= 4 || (halves == 1 && !skewed(p, transpose)))) return false;
+    }
   }
   sh->each_row = len16;
   sh->ahead = p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
