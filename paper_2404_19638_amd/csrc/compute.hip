@@ -126,6 +126,11 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // kz = 16 213 / 206, 32 262 / 252, 64 512 / 480, bfloat16 64 372 / 363; slab rows
 // within the caches: banded, 900,000 entries, kz = 16 26 / 36, kz = 32 39 / 50).
 //
+// Ragged rows past the caches.  They are merged there unless Y is too large (us,
+// cached / past the caches: banded, 5.5M entries, Y of 120 MB, kz = 60, SpMM 172 /
+// 152, fused 212 / 214, bfloat16 110 / 102 and 178 / 152; uniform, Y of 188 MB,
+// bfloat16 kz = 120 SpMM 141 / 130; uniform, Y of 94 MB, kz = 60 80 / 83).
+//
 // Rows of A.  With one vector a lane, loading the slot's row of A for every
 // slot (from L1 mostly) costs less than loading it under a mask where a row
 // starts, unless rows are long: 79.6 against 84.2 us on the 2^24-vertex share
@@ -162,6 +167,7 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   }
   sh->each_row = len16;
   sh->ahead = p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
+  sh->stream = rows * kz * 4 > (int64_t(100) << 20);
   const int64_t G = 64 / sh->lanes;
   const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);
   const int64_t from64 = (fused ? sh->nch == 4 : sh->nch >= 2) ? 4000 : 7000;

@@ -119,7 +119,7 @@ __device__ inline void load_at(const char* __restrict__ base, uint32_t rowoff,
   }
 }
 
-template <int VEC, int LPN, int NCH, bool FULL>
+template <int VEC, int LPN, int NCH, bool FULL, bool STREAM = FULL>
 __device__ inline void put_at(float* __restrict__ row, const LaneCols<VEC, LPN, NCH, FULL>& lc,
                               const float (&acc)[NCH][VEC]) {
 #pragma unroll
@@ -128,7 +128,7 @@ __device__ inline void put_at(float* __restrict__ row, const LaneCols<VEC, LPN, 
     for (int t = 0; t < VEC; t += 4) {
       const f32x4_e4 o = {acc[ch][t], acc[ch][t + 1], acc[ch][t + 2], acc[ch][t + 3]};
       f32x4_e4* y = reinterpret_cast<f32x4_e4*>(row + lc.at[ch] + t);
-      if constexpr (FULL)
+      if constexpr (STREAM)
         __builtin_nontemporal_store(o, y);
       else
         *y = o;   // lanes overlap: let the cache merge them
@@ -181,14 +181,14 @@ __device__ inline void loads_before_stores() {
 // pass, us, step ahead / here: FP32 kz = 32, R-MAT 2^19, 13.6M entries, 251 / 197,
 // 5.5M banded 169 / 128; kz = 60, R-MAT 2^17, 3.4M, 156 / 132; bfloat16 kz = 128,
 // 3.4M, 288 / 184).
-template <int OUTM, int VEC, int LPN, int NCH, bool FULL>
+template <int OUTM, int VEC, int LPN, int NCH, bool FULL, bool STREAM = FULL>
 __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
                                   const LaneCols<VEC, LPN, NCH, FULL>& lc,
                                   const float (&acc)[NCH][VEC]) {
   const int64_t d = OUTM == kAddSlab ? a.Y.map[r] - a.Y.lo : r;
   float* row = a.Y.base + d * a.Y.ld + k0;
   if constexpr (OUTM == kPut) {
-    put_at<VEC, LPN, NCH, FULL>(row, lc, acc);
+    put_at<VEC, LPN, NCH, FULL, STREAM>(row, lc, acc);
   } else {
     float v[NCH][VEC];
     get_at<VEC, LPN, NCH, FULL>(row, lc, v);
@@ -198,20 +198,23 @@ __device__ inline void finish_row(const RunArgs& a, int64_t r, int k0,
   }
 }
 
+enum { kPlain = 0, kAhead = 1, kStream = 2 };
+
 // AROW: how the fused pass gets its rows of A.
 enum { kNoA = 0, kEachSlot = 1, kEachRow = 2 };
 
-// AHEAD: what a row is added to is read where the row starts, its map entry a row
-// before that, instead of where it ends (see pick_run).
+// DEST: kAhead, what a row is added to is read where the row starts, its map entry
+// a row before that, instead of where it ends; kStream, ragged rows are stored past
+// the caches (see pick_run).
 //
 // PARTS: a fused pass over one slice of several.  The slices' dots are summed
 // in a.dots, and the last slice multiplies the sum by the entry's value: a
 // product with a part of the dot could overflow, or be infinite with the other
 // sign, where the product with the whole is not.
 template <typename T, int VEC, int LPN, int NCH, int U, bool FULL, int AROW, int OUTM, bool PARTS,
-          bool AHEAD>
+          int DEST>
 __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
-  constexpr bool FUSED = AROW != kNoA;
+  constexpr bool FUSED = AROW != kNoA, AHEAD = DEST == kAhead;
   constexpr int G = 64 / LPN;
   static_assert(U <= LPN, "one lane per slot of a step");
   using LC = LaneCols<VEC, LPN, NCH, FULL>;
@@ -259,7 +262,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
   float acc[NCH][VEC], lead[NCH][VEC];
   zero(acc);
   zero(lead);
-  // AHEAD: the destination of row r, what it held, and where row r + 1 goes
+  // kAhead: the destination of row r, what it held, and where row r + 1 goes
   float* dst = nullptr;
   float held[NCH][VEC];
   int64_t next = 0;
@@ -280,7 +283,7 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
       add_to<VEC, NCH>(acc, held);
       put_at<VEC, LPN, NCH, FULL>(dst, lc, acc);
     } else {
-      finish_row<OUTM, VEC, LPN, NCH, FULL>(a, r, k0, lc, acc);
+      finish_row<OUTM, VEC, LPN, NCH, FULL, FULL || DEST == kStream>(a, r, k0, lc, acc);
     }
   };
   if constexpr (AHEAD) {
@@ -487,6 +490,7 @@ struct RunShape {
   bool full;         // lanes cover a slice exactly
   bool each_row;     // fused: a row of A is loaded where it starts, not for every slot
   bool ahead;        // adding: a row's destination is read where the row starts
+  bool stream;       // putting: ragged rows are stored past the caches
   int64_t item() const { return (64 / lanes) << lg_s; }
 };
 
@@ -509,10 +513,13 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 #define SPC3D_RUN_H(L, N, U, F, M, O, P)                                       \
   do {                                                                         \
     if constexpr (O == kAddSlab && F && !P && N * VEC <= 8) {                  \
-      if (sh.ahead) SPC3D_RUN_GO(L, N, U, F, M, O, P, true);                   \
-      else SPC3D_RUN_GO(L, N, U, F, M, O, P, false);                           \
+      if (sh.ahead) SPC3D_RUN_GO(L, N, U, F, M, O, P, kAhead);                 \
+      else SPC3D_RUN_GO(L, N, U, F, M, O, P, kPlain);                          \
+    } else if constexpr (O == kPut && !F && !P) {                              \
+      if (sh.stream) SPC3D_RUN_GO(L, N, U, F, M, O, P, kStream);               \
+      else SPC3D_RUN_GO(L, N, U, F, M, O, P, kPlain);                          \
     } else {                                                                   \
-      SPC3D_RUN_GO(L, N, U, F, M, O, P, false);                                \
+      SPC3D_RUN_GO(L, N, U, F, M, O, P, kPlain);                               \
     }                                                                          \
   } while (0)
 #define SPC3D_RUN_A(L, N, U, F, O, P)                                          \
