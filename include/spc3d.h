@@ -250,7 +250,11 @@ spc3d_status spc3d_spmm_buffer_size(spc3d_plan plan, int transpose, int32_t kz, 
  * d_vals[nnz] FP32 in slot order (NULL: s == 1) unless transpose = 2.  X of type x_t (F32 or BF16),
  * accumulation and Y in FP32.  Long rows are split across wavefronts and their
  * partial sums combined in a fixed order, so results are deterministic.
- * d_buf (256-byte aligned) holds at least spc3d_spmm_buffer_size bytes.
+ * d_buf (256-byte aligned) holds at least spc3d_spmm_buffer_size bytes: the
+ * bits of a result follow from the block, the arguments and the inputs'
+ * alignment.  A smaller buffer is refused with SPC3D_ERR_WORKSPACE only if no
+ * shape's carries fit it; where another shape's do, that one is taken, and the
+ * order of a row's sum, so its last bits, may differ.
  * Y may not alias X. */
 spc3d_status spc3d_spmm(spc3d_plan plan, int transpose, const float* d_vals, const void* d_X,
                         spc3d_dtype x_t, int32_t kz, float* d_Y, int mode, int variant,
@@ -263,7 +267,9 @@ spc3d_status spc3d_spmm(spc3d_plan plan, int transpose, const float* d_vals, con
  *   d_Y[i]   (=|+=) sum_{p in row i} s_p * B[j(p)]    (as spc3d_spmm, transpose 0)
  * reading each entry's packed B row once for both.  Arguments as for
  * spc3d_sddmm and spc3d_spmm; d_buf holds spc3d_spmm_buffer_size(plan, 0, kz,
- * variant) bytes.  Neither output may alias an input. */
+ * variant) bytes (a smaller one is taken as spc3d_spmm takes it, which here
+ * may also change the order of a dot's sum, as mode does for wide rows).
+ * The values multiply whole dots, however wide the rows.  Neither output may alias an input. */
 spc3d_status spc3d_sddmm_spmm(spc3d_plan plan, const float* d_vals, const void* d_A,
                               const void* d_B, spc3d_dtype ab_t, int32_t kz, float* d_out,
                               float* d_Y, int mode, int variant, void* d_buf, size_t buf_bytes,
@@ -276,9 +282,10 @@ spc3d_status spc3d_sddmm_spmm(spc3d_plan plan, const float* d_vals, const void* 
  *   d_out[p] (=|+=) s_p * <A[i(p)], B[j(p)]>            (out_mode)
  *   d_dst[(gmap_r[i] - row_lo)*ld_dst + k0 + k] += sum_{p in row i} s_p * B[j(p)*kz + k]
  * for every local row i and k < kz.  Each row sum is complete (summed in the
- * same order as spc3d_sddmm_spmm) before its single addition, so d_dst ends
- * bit for bit as after spc3d_sddmm_spmm (OVERWRITE) followed by
- * spc3d_scatter_reduce(ROWS); rows the block does not touch are unchanged.
+ * same order as spc3d_sddmm_spmm) before its single addition, so d_dst ends,
+ * for any ld_dst, k0 and alignment of d_dst, bit for bit as after
+ * spc3d_sddmm_spmm (OVERWRITE) on the same inputs followed by
+ * spc3d_scatter_reduce(ROWS), both given buffers of the size below; rows the block does not touch are unchanged.
  * Requires 0 <= k0, k0 + kz <= ld_dst; d_dst may not alias an input.  d_buf
  * holds spc3d_spmm_buffer_size(plan, 0, kz, variant) bytes. */
 spc3d_status spc3d_sddmm_spmm_scatter(spc3d_plan plan, const float* d_vals, const void* d_A,
@@ -294,7 +301,8 @@ spc3d_status spc3d_sddmm_spmm_scatter(spc3d_plan plan, const float* d_vals, cons
 /* spc3d_sddmm_spmm for callers that cannot allocate device memory (code under
  * HIP graph capture, tight serving loops, harnesses that forbid hipMalloc):
  * the same computation and results (a default-variant call whose usual shape
- * needs more carries than fit takes a shape with longer work items instead),
+ * needs more carries than fit takes a shape with longer work items instead,
+ * whose sums may differ in their last bits),
  * with the SpMM carries kept in a device
  * array of SPC3D_STATIC_SCRATCH_BYTES that the library holds on each GPU it
  * runs on until the process ends, so no scratch argument is taken and nothing
@@ -386,7 +394,9 @@ spc3d_status spc3d_attention_fwd_buffer_size(spc3d_plan plan, int32_t kz, spc3d_
  * rows rather than NaN.
  * variant: -1, or lg2(lanes per entry) (2..4) | lg2(slots per lane group)
  * << 4 (4..6).  d_buf (256-byte aligned) holds at least
- * spc3d_attention_fwd_buffer_size bytes.  Asynchronous on stream. */
+ * spc3d_attention_fwd_buffer_size bytes; with variant -1 a smaller one is
+ * accepted if longer runs' carries fit it, which may change the last bits.
+ * Asynchronous on stream. */
 spc3d_status spc3d_attention_fwd(spc3d_plan plan, const void* d_Q, const void* d_K,
                                  const void* d_V, spc3d_dtype t, int32_t kz, float* d_out,
                                  float* d_stats, int variant, void* d_buf, size_t buf_bytes,
