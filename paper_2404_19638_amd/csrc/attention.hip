@@ -158,12 +158,6 @@ __device__ inline void row_offset(int i, uint32_t ldb, uint32_t& off) {
 }
 __device__ inline void row_offset(int i, uint32_t ldb, uint64_t& off) { off = (uint64_t)i * ldb; }
 
-template <typename T, int VEC, int NCH>
-__device__ inline void unpack_row(const uint4 (&r)[NCH], float (&o)[NCH][VEC]) {
-#pragma unroll
-  for (int ch = 0; ch < NCH; ++ch) Unpack<T, VEC>::run(r[ch], o[ch]);
-}
-
 // Keeps the conversion of a raw row where it is used: hoisted above the row
 // ends of a step, the converted rows of all its slots would be live together.
 template <int NCH>
@@ -260,7 +254,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(int64_t nnz, int64_t nitems, i
   {
     uint4 q0[NCH];
     load_raw<LPN, NCH>(Q, qoff, q, q0);
-    unpack_row<T, VEC, NCH>(q0, qv);
+    unpack_raw<T, VEC, NCH>(q0, qv);
   }
   bool seen = first;
   const int steps = S / U;
@@ -289,10 +283,10 @@ __global__ __launch_bounds__(256) void k_attn_fwd(int64_t nnz, int64_t nitems, i
     float sc[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if ((hb >> u) & 1u) unpack_row<T, VEC, NCH>(qr[u], qv);
+      if ((hb >> u) & 1u) unpack_raw<T, VEC, NCH>(qr[u], qv);
       float kx[NCH][VEC];
       pin_raw<NCH>(kr[u]);
-      unpack_row<T, VEC, NCH>(kr[u], kx);
+      unpack_raw<T, VEC, NCH>(kr[u], kx);
       float d = 0.f;
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
@@ -326,7 +320,7 @@ __global__ __launch_bounds__(256) void k_attn_fwd(int64_t nnz, int64_t nitems, i
       if (m * U + u < nrun) {
         float vx[NCH][VEC];
         pin_raw<NCH>(vr[u]);
-        unpack_row<T, VEC, NCH>(vr[u], vx);
+        unpack_raw<T, VEC, NCH>(vr[u], vx);
         tri_push(cur, sc[u], before[u], __int_as_float(quad_bcast(y, u)), vx);
       }
     }
