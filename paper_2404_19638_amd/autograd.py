@@ -273,7 +273,14 @@ def _need_fused(Q, Kf, V):
 # 64.9 / 45.1, 31.4M 782 / 773; bfloat16 K = 64 871 / 811).  256 bytes: FP32 2.8M
 # 128 / 120, 3.0M 144 / 147, 7.6M 314 / 336; bfloat16 K = 128 7.6M 369 / 357, 15.5M
 # 763 / 825.  512 bytes: FP32 K = 128 883,000 82.4 / 77.3, 955,000 92.6 / 97.8, 1.8M
-# 147 / 162; bfloat16 K = 256 955,000 111 / 108, 7.6M 663 / 871.
+# 147 / 162; bfloat16 K = 256 955,000 111 / 108, 7.6M 663 / 871.  On uniform and
+# banded blocks the two differ less: 64- and 128-byte rows 0.91 to 1.99 times as
+# fast in one pass from 300,000 to 16M entries (FP32 K = 32: uniform 8M, 20 a row,
+# 364 / 344, banded 5M 148 / 133; the losses: banded 2.6M, half-width 20,000, 98 /
+# 108, K = 16 banded 7.8M 269 / 295, uniform 4M, 33 a row, 117 / 124, R-MAT 2^20,
+# 16M, 378 / 405), 256 bytes on either side of the line 0.97 to 1.10 (FP32 uniform
+# 2M 173 / 161, banded 2M 103 / 98, uniform 2.6M 229 / 216, 16M 1282 / 1269) but
+# for banded blocks past it (5M 308 / 261).
 AUTO_FUSED_F32_MAX_NNZ = 1 << 21
 _AUTO_FUSED_MAX_NNZ = {(spc.F32, 256): AUTO_FUSED_F32_MAX_NNZ, (spc.F32, 512): 900_000,
                        (spc.BF16, 256): 1 << 23, (spc.BF16, 512): 1 << 20}
@@ -308,6 +315,11 @@ def gnn_attention(plan, Q, Kf, V, fused: bool | None = None):
     the one-pass forward is taken for inference (no gradient recorded) where it
     measured faster: rows of up to 128 bytes on every block, wider ones up to a
     number of entries (see _AUTO_FUSED_MAX_NNZ), and the three kernels otherwise.
+
+    Memory: the backward of a block beyond DIRECT_MAX_NNZ entries whose Kf and V
+    both need gradients holds four FP32 values an entry (alpha and the score
+    gradients in column order, and the pairs they are taken from) besides alpha
+    and the score gradients themselves; otherwise one.
     """
     if fused is None:
         fused = _auto_fused(plan, Q, Kf, V)
