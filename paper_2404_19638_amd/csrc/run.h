@@ -23,15 +23,14 @@
 // counts slices.
 //
 // What bounds it: the lines of gathered rows that miss L2.  Against the
-// group-run family (k_spmm), whose index handling and row ends cost about four
-// times the instructions per slot, and which the default took before (us, fused
-// / SpMM, MI355X): the share of a 2^24-vertex R-MAT graph (4.1M entries, kz =
-// 32) 92.6 to 79.6 / 74.2 to 65.7; R-MAT 2^16 kz = 32 45.2 to 28.2 / 33.5 to
-// 23.8, kz = 64 59.5 to 47.7 / 45.6 to 36.4; 2^18 kz = 32 139.9 to 95.6 / 92.1
-// to 79.2; kz = 30 (2^18, degree 16) 122.8 to 81.5 / 85.8 to 66.7; 4096^2
-// with 40,000 entries 13.3 to 10.0 / 12.4 to 9.9.  Loading indices from global
-// memory in the loop instead of staging them costs 20 to 40%: 109 us (fused,
-// the share), 1057 against 834 us (2^20, kz = 64).
+// group-run family (k_spmm), which the default took before: 21.6M against 31.8M
+// vector, 5.0M against 15.5M scalar and 0.9M against 2.2M LDS instructions (the
+// fused pass on the share of a 2^24-vertex R-MAT graph, 4.1M entries, kz = 32), and
+// in us, fused / SpMM, MI355X: the share 92.2 to 78.3 / 72.9 to 63.5; R-MAT 2^16 kz =
+// 32 45.2 to 28.2 / 33.5 to 23.8, kz = 64 59.5 to 47.7 / 45.6 to 36.4; 2^18 kz = 32
+// 139.9 to 95.6 / 92.1 to 79.2; kz = 30 (2^18, degree 16) 122.8 to 81.5 / 85.8 to
+// 66.7.  Loading indices from global memory in the loop instead of staging them
+// costs 20 to 40%: 109 us (fused, the share), 1057 against 834 us (2^20, kz = 64).
 #pragma once
 
 #include <type_traits>
