@@ -41,8 +41,9 @@ constexpr int kBatch = 2;
 //
 // kStreamPacked, nontemporal stores of packed rows, which the pass reads next
 // (cached / nontemporal): 229 MB uniform share 418 / 409, 55 MB R-MAT share 167 /
-// 169.  Rows that are not whole lines gain earlier (kStreamPackedRagged): R-MAT
-// share kz = 40 (69 MB) 295 / 289, 60 (103 MB) 430 / 400, banded kz = 24 (67 MB)
+// 169, banded kz = 16 of two entries a row, 134 MB 418 / 389, uniform kz = 16, 114
+// MB 363 / 368 (and 357 / 368 from cold caches).  Rows that are not whole 64-byte
+// granules gain earlier (kStreamPackedRagged): R-MAT share kz = 40 (69 MB) 295 / 289, 60 (103 MB) 430 / 400, banded kz = 24 (67 MB)
 // 302 / 292, 40 (112 MB) 402 / 369; 24 (41 MB) 222 / 227; of whole lines, 64 (110
 // MB) 305 / 314.
 //
@@ -51,16 +52,23 @@ constexpr int kBatch = 2;
 // 179 / 171 / 172, 220 MB 586 / 585 / 596; banded, 179 MB 395 / 395 / 386, 268 MB
 // 583 / 585 / 573, 537 MB 828 / 831 / 792; 18 MB 172 / 175 / 174.  What is stored
 // cached the next scatter into the same slab may find there: 55 MB 31.8 us against
-// 36.4, 220 MB 113 against 126.  Slab rows that are not whole 64-byte granules
+// 36.4, 220 MB 113 against 126; but what is left there is written back during the
+// step's other kernels, and from 128 MB on (kStreamSlabSpread) that costs more where
+// whole 128-byte lines are spread over a slab larger than the cache (a step that
+// adds to one slab again and again, cached / past the caches: uniform, 229 MB in 916
+// 463 / 455, banded, 268 MB in 1 GB 496 / 484; R-MAT share kz = 128, 220 MB in 220 575
+// / 590; half lines, kz = 16, uniform, 114 MB in 916 366 / 369, banded, 134 MB in 1 GB
+// 389 / 396).  Slab rows that are not whole 64-byte granules
 // (kz, k0 or ld no multiple of 16, or an address) stay cached: a granule that
 // two rows share is then read or written twice (kz = 24, 41 MB 219 / 223 / 226; kz =
 // 60, 103 MB 387 / 400 / 417; banded, 168 MB 510 / 533 / 536).
 constexpr int64_t kStreamSource = 12 << 20;
 constexpr int64_t kStreamSourceConverted = 32 << 20;
-constexpr int64_t kStreamPacked = 128 << 20;
+constexpr int64_t kStreamPacked = 120 << 20;
 constexpr int64_t kStreamPackedRagged = 64 << 20;
 constexpr int64_t kStreamSlab = 32 << 20;
 constexpr int64_t kStreamSlabStored = 256 << 20;
+constexpr int64_t kStreamSlabSpread = 128 << 20;
 
 typedef uint32_t vec4u_e4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t vec4u_e2 __attribute__((ext_vector_type(4), aligned(2)));
@@ -252,7 +260,7 @@ void launch_gather(int64_t n, const int64_t* gmap, int64_t lo, const void* src, 
   const RowSplit sp(n, kz, VO);
   const int64_t from = n * kz * (int64_t)sizeof(Tin), to = n * kz * (int64_t)sizeof(Tout);
   const bool ntld = from > (sizeof(Tin) == sizeof(Tout) ? kStreamSource : kStreamSourceConverted);
-  const bool ntst = to > (kz * sizeof(Tout) % 128 ? kStreamPackedRagged : kStreamPacked);
+  const bool ntst = to > (kz * sizeof(Tout) % 64 ? kStreamPackedRagged : kStreamPacked);
 #define SPC3D_GATHER(LD, ST)                                                                      \
   hipLaunchKernelGGL((k_gather<Tin, Tout, LD, ST>), sp.grid, dim3(256), 0, stream, n, sp.rpw,     \
                      sp.c, sp.magic, gmap, lo, s, ld, k0, kz, d)
@@ -332,7 +340,8 @@ spc3d_status spc3d_scatter_reduce(spc3d_plan h, spc3d_axis axis, const float* d_
     const bool granules = ((kz | k0 | ld_dst) & 15) == 0 &&
                           (reinterpret_cast<uintptr_t>(d_dst) & 63u) == 0;
     const int64_t bytes = granules ? n * kz * 4 : 0;
-    if (bytes > kStreamSlabStored)
+    const bool spread = kz % 32 == 0 && n * ld_dst * 4 > kStreamSlabStored;
+    if (bytes > (spread ? kStreamSlabSpread : kStreamSlabStored))
       hipLaunchKernelGGL((k_scatter_add<true, true>), sp.grid, dim3(256), 0, stream, n, sp.rpw,
                          sp.c, sp.magic, gmap, lo, d_packed, kz, d_dst, ld_dst, k0);
     else if (bytes > kStreamSlab)

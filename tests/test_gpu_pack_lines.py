@@ -1,0 +1,38 @@
+"""Gather and scatter-reduce bit for bit on either side of the lines that depend on
+how rows lie in 64-byte granules and 128-byte lines: packed rows of 120 MB (64 MB
+where they are not whole granules), and slab rows of 128 MB that are whole lines of
+a slab larger than 256 MB."""
+import pytest
+
+from test_gpu_pack_hints import DEV, MB, _plan, _say
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():   # pragma: no cover
+    pytestmark = [pytest.mark.gpu, pytest.mark.skip(reason="no GPU")]
+
+
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("limit,kz", [(120, 32), (120, 16), (120, 48), (64, 40)])
+def test_packed_rows(limit, kz, over):
+    n = limit * MB // (4 * kz) + over
+    spc, plan = _plan(n)
+    _say(f"packed lines: n={n} kz={kz}")
+    S = torch.rand((2 * n, kz + 4), device=DEV,
+                   generator=torch.Generator(device=DEV).manual_seed(n))
+    assert torch.equal(spc.gather(plan, spc.ROWS, S, 4, kz), S[::2, 4:])
+
+
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("kz,ld", [(32, 64), (32, 128), (32, 80), (16, 64), (64, 64)])
+def test_slab_rows(kz, ld, over):
+    n = 128 * MB // (4 * kz) + over
+    spc, plan = _plan(n)
+    _say(f"slab lines: n={n} kz={kz} ld={ld}")
+    g = torch.Generator(device=DEV).manual_seed(n)
+    packed = torch.rand((n, kz), device=DEV, generator=g)
+    dst = torch.rand((2 * n, ld), device=DEV, generator=g)
+    want = dst.clone()
+    want[::2, ld - kz:] += packed
+    spc.scatter_reduce(plan, spc.ROWS, packed, dst, ld - kz)
+    assert torch.equal(dst, want)
