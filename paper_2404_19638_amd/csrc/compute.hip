@@ -126,6 +126,17 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // kz = 16 213 / 206, 32 262 / 252, 64 512 / 480, bfloat16 64 372 / 363; slab rows
 // within the caches: banded, 900,000 entries, kz = 16 26 / 36, kz = 32 39 / 50).
 //
+// Steps of 4 with two vectors a lane, which hold two wavefronts a SIMD fewer but
+// twice the rows in flight, pay where rows are put and a row end costs little: in
+// SpMM (us, steps of 2 / 4: FP32 kz = 64 banded, 11 a row, 134 / 120, 5 a row 85.4 /
+// 80.5, uniform, 16 a row, 98.4 / 96.3, R-MAT 2^17, 23 a row, 44.1 / 43.2; kz = 60
+// banded, 11 a row, 157 / 144, 2 a row 416 / 382) but for ragged FP32 rows of 12
+// entries and more on skewed columns (R-MAT 2^17 kz = 48 39.0 / 40.9, 60 51.7 / 54.1;
+// 2^19, 16 a row, 123 / 126; 2^20, 10 a row, 131.5 / 131.0), and in the fused pass
+// below 4 entries a row (uniform, 2.2, kz = 64 350 / 345, 60 494 / 485, bfloat16 kz =
+// 100 563 / 544, 3.9 kz = 64 511 / 505; 8.7 a row 100.5 / 103.1; banded, 11 a row,
+// 156 / 160, 5 a row, bfloat16 kz = 100 148 / 157).
+//
 // Ragged rows past the caches.  They are merged there unless Y is too large (us,
 // cached / past the caches: banded, 5.5M entries, Y of 120 MB, kz = 60, SpMM 172 /
 // 152, fused 212 / 214, bfloat16 110 / 102 and 178 / 152; uniform, Y of 188 MB,
@@ -167,6 +178,8 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
   }
   sh->each_row = len16;
   sh->ahead = p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
+  sh->step4 = fused ? p->nnz < 4 * rows
+                    : sh->full || t == SPC3D_BF16 || p->nnz < 12 * rows || !skewed(p, transpose);
   sh->stream = rows * kz * 4 > (int64_t(100) << 20);
   const int64_t G = 64 / sh->lanes;
   const bool long_runs = len16 || (!fused && sh->nch < 4 && p->nnz >= 8 * rows);

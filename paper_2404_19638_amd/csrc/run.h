@@ -489,6 +489,7 @@ struct RunShape {
   bool full;         // lanes cover a slice exactly
   bool each_row;     // fused: a row of A is loaded where it starts, not for every slot
   bool ahead;        // adding: a row's destination is read where the row starts
+  bool step4;        // putting: steps of 4 slots with two vectors a lane
   bool stream;       // putting: ragged rows are stored past the caches
   int64_t item() const { return (64 / lanes) << lg_s; }
 };
@@ -531,7 +532,8 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 // slices of a fused pass are 8 or 16 vectors, which 8 lanes cover
 #define SPC3D_RUN_OUT(L, N, U, F, O)                                           \
   do {                                                                         \
-    if constexpr (FUSED && (F || (VEC == 8 && N == 2 && O != kPut)) && L == 8 && N <= 2) {                            \
+    if constexpr (FUSED && L == 8 && N <= 2 &&                                 \
+                  (F || (VEC == 8 && N == 2 && O != kPut))) {                  \
       if (sh.slices > 1) SPC3D_RUN_A(L, N, U, F, O, true);                     \
       else SPC3D_RUN_A(L, N, U, F, O, false);                                  \
     } else {                                                                   \
@@ -547,7 +549,8 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
 // Steps of 2 slots with two vectors a lane and of 1 with four: with steps twice
 // as long two wavefronts a SIMD fewer fit (us, steps of 4 / 2, R-MAT 2^17, 3.4M
 // entries: bfloat16 kz = 128 fused 107 / 104, folded 184 / 157; FP32 kz = 40
-// folded 123 / 115; of 2 / 1, FP32 kz = 128 folded 231 / 178).  Adding, two
+// folded 123 / 115; of 2 / 1, FP32 kz = 128 folded 231 / 178).  But steps of 4 with
+// two vectors where rows are put and RunShape::step4 says so.  Adding, two
 // bfloat16 vectors a lane take the general form, which fits 128 registers where
 // the full one takes 129 (folded 156 / 130).
 #define SPC3D_RUN_SHAPE(L, N, U)                                                    \
@@ -557,6 +560,12 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
   }
   SPC3D_RUN_SHAPE(4, 1, 4)
   SPC3D_RUN_SHAPE(8, 1, 4)
+  if (outm == kPut && sh.step4 && sh.lanes == 8 && sh.nch == 2 &&
+      (!FUSED || sh.slices == 1)) {
+    if (sh.full) SPC3D_RUN_A(8, 2, 4, true, kPut, false);
+    else SPC3D_RUN_A(8, 2, 4, false, kPut, false);
+    return;
+  }
   SPC3D_RUN_SHAPE(8, 2, 2)
   SPC3D_RUN_SHAPE(8, 4, 1)
 #undef SPC3D_RUN_SHAPE
