@@ -42,10 +42,10 @@ constexpr int kBatch = 2;
 // kStreamPacked, nontemporal stores of packed rows, which the pass reads next
 // (cached / nontemporal): 229 MB uniform share 418 / 409, 55 MB R-MAT share 167 /
 // 169, banded kz = 16 of two entries a row, 134 MB 418 / 389, uniform kz = 16, 114
-// MB 363 / 368 (and 357 / 368 from cold caches).  Rows that are not whole 64-byte
-// granules gain earlier (kStreamPackedRagged): R-MAT share kz = 40 (69 MB) 295 / 289, 60 (103 MB) 430 / 400, banded kz = 24 (67 MB)
-// 302 / 292, 40 (112 MB) 402 / 369; 24 (41 MB) 222 / 227; of whole lines, 64 (110
-// MB) 305 / 314.
+// MB 363 / 368 (and 357 / 368 from cold caches).  Rows that are not whole 64-byte granules gain earlier
+// (kStreamPackedRagged): R-MAT share kz = 40, 69 MB 270 / 282, banded, 11 a row, 80 MB
+// 292 / 305, 3 a row, kz = 20, 84 MB 295 / 286, bfloat16 kz = 40, 84 MB 450 / 431,
+// kz = 30, 126 MB 454 / 421; share kz = 60 (103 MB) 430 / 400.
 //
 // kStreamSlab, nontemporal loads of the slab rows a scatter adds to, and
 // kStreamSlabStored, of the stores as well (cached / loads / both): R-MAT share, 55 MB
@@ -53,21 +53,22 @@ constexpr int kBatch = 2;
 // 583 / 585 / 573, 537 MB 828 / 831 / 792; 18 MB 172 / 175 / 174.  What is stored
 // cached the next scatter into the same slab may find there: 55 MB 31.8 us against
 // 36.4, 220 MB 113 against 126; but what is left there is written back during the
-// step's other kernels, and from 128 MB on (kStreamSlabSpread) that costs more where
-// whole 128-byte lines are spread over a slab larger than the cache (a step that
-// adds to one slab again and again, cached / past the caches: uniform, 229 MB in 916
-// 463 / 455, banded, 268 MB in 1 GB 496 / 484; R-MAT share kz = 128, 220 MB in 220 575
-// / 590; half lines, kz = 16, uniform, 114 MB in 916 366 / 369, banded, 134 MB in 1 GB
-// 389 / 396).  Slab rows that are not whole 64-byte granules
+// step's other kernels, which costs more where the slab rows near the cache's size, and
+// from 128 MB on (kStreamSlabSpread) where whole 128-byte lines of a slab row are
+// taken and all of those rows are larger than it (a step that adds to one slab again
+// and again, cached / past the caches: uniform, 229 of 916 MB 463 / 455, banded, 268 MB
+// of 1 GB 496 / 484; whole rows, banded, 5 a row, bfloat16 kz = 128, 256 MB 469 / 431,
+// R-MAT share kz = 128, 220 MB 575 / 590; half lines, kz = 16, uniform, 114 of 916 MB
+// 366 / 369, banded, 134 MB of 1 GB 389 / 396).  Slab rows that are not whole 64-byte granules
 // (kz, k0 or ld no multiple of 16, or an address) stay cached: a granule that
 // two rows share is then read or written twice (kz = 24, 41 MB 219 / 223 / 226; kz =
 // 60, 103 MB 387 / 400 / 417; banded, 168 MB 510 / 533 / 536).
 constexpr int64_t kStreamSource = 12 << 20;
 constexpr int64_t kStreamSourceConverted = 32 << 20;
 constexpr int64_t kStreamPacked = 120 << 20;
-constexpr int64_t kStreamPackedRagged = 64 << 20;
+constexpr int64_t kStreamPackedRagged = 78 << 20;
 constexpr int64_t kStreamSlab = 32 << 20;
-constexpr int64_t kStreamSlabStored = 256 << 20;
+constexpr int64_t kStreamSlabStored = 220 << 20;
 constexpr int64_t kStreamSlabSpread = 128 << 20;
 
 typedef uint32_t vec4u_e4 __attribute__((ext_vector_type(4), aligned(4)));

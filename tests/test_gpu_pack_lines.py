@@ -1,7 +1,7 @@
 """Gather and scatter-reduce bit for bit on either side of the lines that depend on
-how rows lie in 64-byte granules and 128-byte lines: packed rows of 120 MB (64 MB
-where they are not whole granules), and slab rows of 128 MB that are whole lines of
-a slab larger than 256 MB."""
+how rows lie in 64-byte granules and 128-byte lines: packed rows of 120 MB (78 MB
+where they are not whole granules), and slab rows of 220 MB (128 MB of a larger
+slab)."""
 import pytest
 
 from test_gpu_pack_hints import DEV, MB, _plan, _say
@@ -13,7 +13,7 @@ if not torch.cuda.is_available():   # pragma: no cover
 
 
 @pytest.mark.parametrize("over", [0, 1])
-@pytest.mark.parametrize("limit,kz", [(120, 32), (120, 16), (120, 48), (64, 40)])
+@pytest.mark.parametrize("limit,kz", [(120, 32), (120, 16), (120, 48), (78, 40)])
 def test_packed_rows(limit, kz, over):
     n = limit * MB // (4 * kz) + over
     spc, plan = _plan(n)
@@ -24,9 +24,10 @@ def test_packed_rows(limit, kz, over):
 
 
 @pytest.mark.parametrize("over", [0, 1])
-@pytest.mark.parametrize("kz,ld", [(32, 64), (32, 128), (32, 80), (16, 64), (64, 64)])
-def test_slab_rows(kz, ld, over):
-    n = 128 * MB // (4 * kz) + over
+@pytest.mark.parametrize("limit,kz,ld", [(128, 32, 64), (128, 32, 128), (128, 32, 80),
+                                         (128, 16, 64), (220, 16, 64), (220, 64, 64)])
+def test_slab_rows(limit, kz, ld, over):
+    n = limit * MB // (4 * kz) + over
     spc, plan = _plan(n)
     _say(f"slab lines: n={n} kz={kz} ld={ld}")
     g = torch.Generator(device=DEV).manual_seed(n)
