@@ -120,11 +120,18 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // and 1616 / 1583.
 //
 // Destinations ahead.  Adding to a slab whose rows come from HBM, on rows so short
-// that nearly every step ends some, a destination read where its row ends is
-// waited for each time; read where the row starts it costs a row of registers
-// (folded, us, at the end / at the start: uniform, 4.0M entries, 2.2 a row, FP32
-// kz = 16 213 / 206, 32 262 / 252, 64 512 / 480, bfloat16 64 372 / 363; slab rows
-// within the caches: banded, 900,000 entries, kz = 16 26 / 36, kz = 32 39 / 50).
+// that nearly every step ends some, a destination read where its row ends is waited
+// for each time; read with the step's gathered rows it costs registers (folded, us,
+// where the row ends / with the step, two vectors a lane in steps of 4: uniform, 4.0M
+// entries, 2.2 a row, FP32 kz = 16 216 / 195, 32 263 / 252, 64 514 / 489, bfloat16 kz =
+// 64 370 / 362; banded, 2 a row, 4.2M 213 / 198, 259 / 250, 490 / 461, 367 / 364; 3 a
+// row, 3.1M 116 / 114, 162 / 162, 301 / 277, 235 / 224.  Uniform, 3.9 a row, 8M 332 /
+// 319, 363 / 372, 730 / 712, 499 / 516; 4.1 a row, slab rows of 25 MB, kz = 16 63 / 64,
+// of 50, kz = 32 72 / 77; banded, 11 a row, 95 / 103, 119 / 141).  FP32 rows on 4 lanes,
+// 16 groups a wavefront that each wait, take it below 10 entries a row at any size
+// (kz = 16: the share at 9.3, a whole step 135 / 123; uniform, 8.7 59 / 58; banded,
+// 226,000 entries, 2 a row, 14.9 / 13.5; uniform, 16 a row, 47.6 / 55.8).  Read where the row
+// starts instead: kz = 16 208, 213 and 115, 32 251, 258 and 157, 64 478, 473 and 272.
 //
 // Steps of 4 with two vectors a lane, which hold two wavefronts a SIMD fewer but
 // twice the rows in flight, pay where rows are put and a row end costs little: in
@@ -177,7 +184,9 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
     }
   }
   sh->each_row = len16;
-  sh->ahead = p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
+  sh->ahead = t == SPC3D_F32 && sh->lanes == 4
+                  ? p->nnz < 10 * rows
+                  : p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
   sh->step4 = fused ? p->nnz < 4 * rows
                     : sh->full || t == SPC3D_BF16 || p->nnz < 12 * rows || !skewed(p, transpose);
   sh->stream = rows * kz * 4 > (int64_t(100) << 20);

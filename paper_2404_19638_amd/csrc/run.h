@@ -175,9 +175,9 @@ __device__ inline void loads_before_stores() {
 }
 
 // Puts (or adds) the finished local row r.  What a row is added to is read
-// here, where the row ends.  Read a step ahead, with the gathered rows, it held
-// U rows more in registers, which cost more wavefronts than the wait (folded
-// pass, us, step ahead / here: FP32 kz = 32, R-MAT 2^19, 13.6M entries, 251 / 197,
+// here, where the row ends.  Read with the step's gathered rows (kAhead) it holds U
+// rows more in registers, which costs more wavefronts than the wait saves but on
+// very short rows of cold slabs (folded pass, us, with the step / here: FP32 kz = 32, R-MAT 2^19, 13.6M entries, 251 / 197,
 // 5.5M banded 169 / 128; kz = 60, R-MAT 2^17, 3.4M, 156 / 132; bfloat16 kz = 128,
 // 3.4M, 288 / 184).
 template <int OUTM, int VEC, int LPN, int NCH, bool FULL, bool STREAM = FULL>
@@ -202,8 +202,8 @@ enum { kPlain = 0, kAhead = 1, kStream = 2 };
 // AROW: how the fused pass gets its rows of A.
 enum { kNoA = 0, kEachSlot = 1, kEachRow = 2 };
 
-// DEST: kAhead, what a row is added to is read where the row starts, its map entry
-// a row before that, instead of where it ends; kStream, ragged rows are stored past
+// DEST: kAhead, what the rows that end in a step are added to is read with the step's
+// gathered rows, their map entries a step before that; kStream, ragged rows are stored past
 // the caches (see pick_run).
 //
 // PARTS: a fused pass over one slice of several.  The slices' dots are summed
@@ -261,34 +261,9 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
   float acc[NCH][VEC], lead[NCH][VEC];
   zero(acc);
   zero(lead);
-  // kAhead: the destination of row r, what it held, and where row r + 1 goes
-  float* dst = nullptr;
-  float held[NCH][VEC];
-  int64_t next = 0;
-  auto place_of = [&](int rr) {
-    if constexpr (OUTM == kAddSlab)
-      next = rr < (int)a.Y.n ? a.Y.map[rr] - a.Y.lo : 0;
-    else
-      next = rr;
-  };
-  auto start_row = [&]() {   // row r, whose place was looked up
-    dst = a.Y.base + next * a.Y.ld + k0;
-    get_at<VEC, LPN, NCH, FULL>(dst, lc, held);
-    place_of(r + 1);
-  };
   auto end_row = [&]() {
-    if constexpr (AHEAD) {
-      loads_before_stores<FULL>();
-      add_to<VEC, NCH>(acc, held);
-      put_at<VEC, LPN, NCH, FULL>(dst, lc, acc);
-    } else {
-      finish_row<OUTM, VEC, LPN, NCH, FULL, FULL || DEST == kStream>(a, r, k0, lc, acc);
-    }
+    finish_row<OUTM, VEC, LPN, NCH, FULL, FULL || DEST == kStream>(a, r, k0, lc, acc);
   };
-  if constexpr (AHEAD) {
-    place_of(first ? r : r + 1);
-    if (first) start_row();
-  }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
@@ -297,6 +272,13 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
     const int steps = S / U;
     uint4 acur[AROW == kEachRow ? NCH : 1];   // the current row of A
     if constexpr (AROW == kEachRow) load_at<T, VEC, LPN, NCH, FULL>(A, aoff, lc, acur);
+    int64_t place[AHEAD ? U : 1];
+    auto look_up = [&](uint32_t ends, int rr) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if ((ends >> u) & 1u) place[u] = a.Y.map[rr++];   // used a step later
+    };
+    if constexpr (AHEAD) look_up((uint32_t)run & ((1u << U) - 1u), r);
     for (int m = 0; m < steps; ++m) {
       int32_t col[U], vb[U];
       read_words<U>(s_col + g * P + m * U, col);
@@ -321,6 +303,18 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
           }
         }
       }
+      float held[AHEAD ? U : 1][NCH][VEC];
+      float* dst[AHEAD ? U : 1];
+      if constexpr (AHEAD) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if ((hb >> u) & 1u) {
+            dst[u] = a.Y.base + (place[u] - a.Y.lo) * a.Y.ld + k0;
+            get_at<VEC, LPN, NCH, FULL>(dst[u], lc, held[u]);
+          }
+        }
+        if (m + 1 < steps) look_up((uint32_t)run & ((1u << U) - 1u), r + __popc(hb));
+      }
       float res = 0.f;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -328,10 +322,15 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
         float xv[NCH][VEC];
         unpack_raw<T, VEC, NCH>(x[u], xv);
         if ((hb >> u) & 1u) {   // the row before this slot is complete
-          if (seen)
-            end_row();
-          else
+          if (!seen) {
             copy_to<VEC, NCH>(lead, acc);
+          } else if constexpr (AHEAD) {
+            loads_before_stores<FULL>();
+            add_to<VEC, NCH>(acc, held[u]);
+            put_at<VEC, LPN, NCH, FULL>(dst[u], lc, acc);
+          } else {
+            end_row();
+          }
           zero(acc);
           if constexpr (AROW == kEachRow) {
 #pragma unroll
@@ -339,7 +338,6 @@ __global__ __launch_bounds__(256) void k_run(const RunArgs a) {
           }
           ++r;
           seen = true;
-          if constexpr (AHEAD) start_row();
         }
         if constexpr (FUSED) {
           float av[NCH][VEC];
@@ -488,7 +486,7 @@ struct RunShape {
   int kw, slices;    // elements per slice, slices of a row
   bool full;         // lanes cover a slice exactly
   bool each_row;     // fused: a row of A is loaded where it starts, not for every slot
-  bool ahead;        // adding: a row's destination is read where the row starts
+  bool ahead;        // adding: destinations are read with a step's gathered rows
   bool step4;        // putting: steps of 4 slots with two vectors a lane
   bool stream;       // putting: ragged rows are stored past the caches
   int64_t item() const { return (64 / lanes) << lg_s; }
@@ -512,8 +510,9 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
   } while (0)
 #define SPC3D_RUN_H(L, N, U, F, M, O, P)                                       \
   do {                                                                         \
-    if constexpr (O == kAddSlab && F && !P && N * VEC <= 8) {                  \
-      if (sh.ahead) SPC3D_RUN_GO(L, N, U, F, M, O, P, kAhead);                 \
+    if constexpr (O == kAddSlab && !P && N * VEC <= 8 &&                       \
+                  (F || (VEC == 4 && L == 4))) {                               \
+      if (sh.ahead) SPC3D_RUN_GO(L, N, 4, F, M, O, P, kAhead);                 \
       else SPC3D_RUN_GO(L, N, U, F, M, O, P, kPlain);                          \
     } else if constexpr (O == kPut && !F && !P) {                              \
       if (sh.stream) SPC3D_RUN_GO(L, N, U, F, M, O, P, kStream);               \
