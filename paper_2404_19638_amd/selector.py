@@ -27,19 +27,23 @@ from . import tune
 NFEAT = spc.NFEAT
 TARGET_CAP = 3.0  # slowdowns beyond 8x are all "bad"; capping keeps them from dominating the loss
 # The library default (variant -1) is kept unless another candidate is predicted
-# faster by more than this (log2): the default is within 1.5% of the fastest in the
+# faster by more than this (log2): the default is within 1.3% of the fastest in the
 # geometric mean, and the smaller gains that a network predicts on blocks it has not
-# seen are mostly not there.  Regret there at margins 1.03 / 1.12 / 1.2 / 1.3 / 1.5 /
-# always the default, % (384 blocks in four parts, each judged by a network trained
-# on the others): SDDMM 1.73 / 1.56 / 1.481 / 1.475 / 1.453 / 1.448, SpMM 1.49 / 1.47
-# / 1.448 / 1.447 / 1.447 / 1.447, fused 0.92 / 0.83 / 0.808 / 0.806 / 0.799 / 0.799.
+# seen are mostly not there.  Regret there beyond that of always keeping the default,
+# at margins 1.00 / 1.03 / 1.12 / 1.2 / 1.3 / 1.5, % (384 blocks in four parts, each
+# judged by a network trained on the others): SDDMM 0.61 / 0.31 / 0.12 / 0.04 / 0.02 /
+# 0.01, SpMM -0.06 / 0.00 / 0.02 / 0.00 / 0.00 / 0.00 (0.06 the first's error), fused
+# 0.15 / 0.14 / 0.04 / 0.01 / 0.00 / 0.00.
 KEEP_DEFAULT_MARGIN = math.log2(1.3)
 # Margins tried per operation on the training blocks; inf keeps the default always.
 MARGIN_GRID = (0.0, math.log2(1.02), math.log2(1.03), math.log2(1.05), math.log2(1.08),
                math.log2(1.12), math.log2(1.2), math.log2(1.3), math.log2(1.5), math.inf)
-# Where keeping the default always is best, a margin of KEEP_DEFAULT_MARGIN or more
-# is still taken if its mean log slowdown is within this of that: a fifth of what
-# the labels resolve (3% a timing, 3072 instances).
+# A margin below KEEP_DEFAULT_MARGIN must beat keeping the default always by this many
+# standard errors of the difference between blocks: SpMM's 1.00 came out 0.06% better
+# on unseen training blocks, within the error, and 0.12% worse on the held-out ones.  A
+# larger one is taken if its mean log slowdown is within MARGIN_SLACK of keeping the
+# default: a fifth of what the labels resolve (3% a timing, 3072 instances).
+MARGIN_ERRORS = 2.0
 MARGIN_SLACK = 1e-4
 
 
@@ -236,25 +240,34 @@ class Selector:
     def fit_margin(self, op: str, recs: list, grid=MARGIN_GRID, folds: int = 4,
                    steps: int = 3000) -> float:
         """Chooses the operation's keep-default margin: the one of the grid with
-        the least geometric-mean regret against the autotuner (ties go to the
-        larger margin; see MARGIN_SLACK) on blocks that the network choosing has not seen.  Each
-        of `folds` parts of the records' blocks is judged by a network trained
+        the least geometric-mean regret against the autotuner on blocks that the
+        network choosing has not seen, where that is clearly below the default's
+        (MARGIN_ERRORS); else the smallest large one that costs nothing (MARGIN_SLACK).
+        Each of `folds` parts of the records' blocks is judged by a network trained
         on the others: judged on its own training blocks, a network that has
         learned their noise is given too small a margin."""
         blocks = sorted({r["block"] for r in recs})
-        total = np.zeros(len(grid))
+        losses = []   # per block, the mean log slowdown at each margin
         for f in range(folds):
             out = set(blocks[f::folds])
             part = Selector(self.hidden, self.seed, self.device)
             part.fit(op, *dataset([r for r in recs if r["block"] not in out], op), steps=steps)
-            total += part.margin_losses(op, [r for r in recs if r["block"] in out], grid).sum(1)
-        n = sum(r["op"] == op for r in recs)
-        best = min(range(len(grid)), key=lambda i: (total[i], -grid[i]))
-        if math.isinf(grid[best]):
-            best = min((i for i, m in enumerate(grid) if m >= KEEP_DEFAULT_MARGIN
-                        and total[i] <= total[best] + MARGIN_SLACK * n), key=lambda i: grid[i])
-        self.margins[op] = grid[best]
-        return grid[best]
+            judged = [r for r in recs if r["block"] in out and r["op"] == op]
+            lost = part.margin_losses(op, judged, (*grid, math.inf))
+            of = np.array([r["block"] for r in judged])
+            losses += [lost[:, of == b].mean(1) for b in sorted(out)]
+        extra = np.array(losses)
+        extra = extra[:, :-1] - extra[:, -1:]   # against keeping the default always
+        mean, err = extra.mean(0), extra.std(0) / math.sqrt(len(extra))
+        clear = [i for i in range(len(grid)) if mean[i] < -MARGIN_ERRORS * err[i]]
+        free = [i for i, m in enumerate(grid)
+                if m >= KEEP_DEFAULT_MARGIN and mean[i] <= MARGIN_SLACK]
+        if clear:
+            best = min(clear, key=lambda i: (mean[i], -grid[i]))
+        else:
+            best = min(free, key=lambda i: grid[i]) if free else None
+        self.margins[op] = math.inf if best is None else grid[best]
+        return self.margins[op]
 
     def in_range(self, op: str, f: np.ndarray, margin: float = 0.0) -> bool:
         """True when every feature lies within the training range (+- margin).
