@@ -130,7 +130,14 @@ int slice_count(const Plan* p, int transpose, bool fused, int64_t row_bytes) {
 // of 50, kz = 32 72 / 77; banded, 11 a row, 95 / 103, 119 / 141).  FP32 rows on 4 lanes,
 // 16 groups a wavefront that each wait, take it below 10 entries a row at any size
 // (kz = 16: the share at 9.3, a whole step 135 / 123; uniform, 8.7 59 / 58; banded,
-// 226,000 entries, 2 a row, 14.9 / 13.5; uniform, 16 a row, 47.6 / 55.8).  Read where the row
+// 226,000 entries, 2 a row, 14.9 / 13.5; uniform, 16 a row, 47.6 / 55.8).  On 8 lanes
+// FP32 rows take it where there are no more than 4 wavefronts a SIMD, with two
+// vectors a lane 2, for which the registers suffice, and below 20 entries a row
+// (whole steps: kz = 32 R-MAT 2^16, 494,000, 15 a row, 33.7 / 30.8, kz = 20 32.9 / 30.1,
+// 575,000, 26 a row, 31.6 / 32.6, uniform, 600,000 34.0 / 38.8, 284,000, 28 a row, 17.7 /
+// 20.6; kz = 64 banded, 239,000, 5 a row, 38.8 / 34.6, kz = 40 37.2 / 32.6, R-MAT 2^15,
+// 244,000 35.4 / 31.1, 2^16 41.3 / 43.5, uniform, 284,000 24.9 / 25.9; bfloat16 kz = 64
+// 239,000 28.7 / 32.4).  Read where the row
 // starts instead: kz = 16 208, 213 and 115, 32 251, 258 and 157, 64 478, 473 and 272.
 //
 // Steps of 4 with two vectors a lane, which hold two wavefronts a SIMD fewer but
@@ -184,9 +191,6 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
     }
   }
   sh->each_row = len16;
-  sh->ahead = t == SPC3D_F32 && sh->lanes == 4
-                  ? p->nnz < 10 * rows
-                  : p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20);
   sh->step4 = fused ? p->nnz < 4 * rows
                     : sh->full || t == SPC3D_BF16 || p->nnz < 12 * rows || !skewed(p, transpose);
   sh->stream = rows * kz * 4 > (int64_t(100) << 20);
@@ -201,6 +205,11 @@ bool pick_run(const Plan* p, int transpose, bool fused, int kz, spc3d_dtype t, b
              : p->nnz >= from16 * 16 * G                            ? 4
              : p->nnz >= from8 * 8 * G                              ? 3
                                                                     : 2;
+  const int64_t waves = p->nnz / (G << sh->lg_s);
+  sh->ahead = (sh->full && p->nnz < 3 * rows && rows * kz * 4 >= (int64_t(48) << 20)) ||
+              (t == SPC3D_F32 &&
+               (sh->lanes == 4 ? p->nnz < 10 * rows
+                               : p->nnz < 20 * rows && waves < (sh->nch == 1 ? 4096 : 2048)));
   return true;
 }
 

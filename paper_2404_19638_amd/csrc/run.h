@@ -510,8 +510,7 @@ void launch_run(const RunShape& sh, RunArgs a, int outm, const int32_t* ptr, int
   } while (0)
 #define SPC3D_RUN_H(L, N, U, F, M, O, P)                                       \
   do {                                                                         \
-    if constexpr (O == kAddSlab && !P && N * VEC <= 8 &&                       \
-                  (F || (VEC == 4 && L == 4))) {                               \
+    if constexpr (O == kAddSlab && !P && N * VEC <= 8 && (F || VEC == 4)) {    \
       if (sh.ahead) SPC3D_RUN_GO(L, N, 4, F, M, O, P, kAhead);                 \
       else SPC3D_RUN_GO(L, N, U, F, M, O, P, kPlain);                          \
     } else if constexpr (O == kPut && !F && !P) {                              \
